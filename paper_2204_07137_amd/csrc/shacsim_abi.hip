@@ -773,28 +773,6 @@ static int fill_mlp(MlpArgsT<T>& P, int nl, const int* dims, const void* const* 
   return SIM_OK;
 }
 
-template <typename T>
-static int launch_transposes(const MlpArgsT<T>& P, void* s);
-template <>
-int launch_transposes<float>(const MlpArgsT<float>& P, void* s) {
-  for (int l = 0; l < P.nl; ++l) {
-    int bad = P.bf16 ? sim_f32::launch_prep_bf16(P.src[l], const_cast<uint16_t*>(P.Pf[l]), const_cast<uint16_t*>(P.Pb[l]),
-                                                 P.dims[l + 1], P.dims[l], s)
-                     : sim_f32::launch_prep_weights(P.src[l], const_cast<float*>(P.WT[l]), const_cast<float*>(P.W[l]),
-                                                    P.dims[l + 1], P.dims[l], s);
-    if (bad) return -1;
-  }
-  return 0;
-}
-template <>
-int launch_transposes<double>(const MlpArgsT<double>& P, void* s) {
-  for (int l = 0; l < P.nl; ++l)
-    if (sim_f64::launch_prep_weights(P.src[l], const_cast<double*>(P.WT[l]), const_cast<double*>(P.W[l]),
-                                     P.dims[l + 1], P.dims[l], s))
-      return -1;
-  return 0;
-}
-
 // ---------------------------------------------------------------- argument building
 template <typename T>
 static int build_forward_args(SimHandle* h, const SimForwardIO* io, WinArgsT<T>& A) {
@@ -969,14 +947,8 @@ static void build_theta_args(SimHandle* h, const SimAdjointIO* io, ThetaArgsT<T>
 }
 
 // ---------------------------------------------------------------- launches (FP32 / FP64)
-static int do_prep(const WinArgsT<float>& A, void* s) {
-  int bad = A.closed_loop ? launch_transposes(A.actor, s) : 0;
-  return bad | launch_transposes(A.critic, s);
-}
-static int do_prep(const WinArgsT<double>& A, void* s) {
-  int bad = A.closed_loop ? launch_transposes(A.actor, s) : 0;
-  return bad | launch_transposes(A.critic, s);
-}
+static int do_prep(const WinArgsT<float>& A, void* s) { return sim_f32::launch_prep(A, s); }
+static int do_prep(const WinArgsT<double>& A, void* s) { return sim_f64::launch_prep(A, s); }
 static int do_window(const WinArgsT<float>& A, int adjoint, int plain, int S, int nv, int mtu, int lanes, void* s) {
   return adjoint ? sim_f32::launch_adjoint(A, plain, S, nv, mtu, lanes, s)
                  : sim_f32::launch_forward(A, plain, S, nv, mtu, lanes, s);

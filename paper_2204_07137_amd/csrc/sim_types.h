@@ -308,8 +308,7 @@ struct CriticFitT {
   namespace NS {                                                                            \
   int launch_forward(const WinArgsT<T>& A, int plain, int substeps, int nv, int mtu, int lanes, void* stream); \
   int launch_adjoint(const WinArgsT<T>& A, int plain, int substeps, int nv, int mtu, int lanes, void* stream); \
-  int launch_prep_weights(const T* W, T* WT, T* Wp, int n_out, int n_in, void* stream);   \
-  int launch_prep_bf16(const T* W, uint16_t* Pf, uint16_t* Pb, int n_out, int n_in, void* stream); \
+  int launch_prep(const WinArgsT<T>& A, void* stream);                                     \
   int launch_theta(const ThetaArgsT<T>& A, void* stream);                                  \
   int launch_group(const GroupArgsT<T>& G, int adjoint, int mtu, size_t lds_bytes, void* stream); \
   size_t group_lds_bytes(int lanes, int mtu);                                              \
