@@ -460,6 +460,13 @@ typedef struct SimCriticFitIO {
  * count + rows.  Pairwise (Chan-Golub-LeVeque) update with FP64 sums in a fixed order. */
 int sim_obs_stats_update(const void* obs, long rows, int dim, double count, void* mean, void* var, void* inv_std,
                          double eps, int precision, void* hip_stream);
+/* The same with a device workspace, which spreads a large batch over the whole GPU:
+ * sim_obs_stats_workspace_bytes(rows, dim) bytes, aligned to 8 (0 for small batches, which need
+ * none: workspace may then be null).  The workspace is free again once the call's work on
+ * hip_stream is done. */
+size_t sim_obs_stats_workspace_bytes(long rows, int dim);
+int sim_obs_stats_update_ws(const void* obs, long rows, int dim, double count, void* mean, void* var, void* inv_std,
+                            double eps, int precision, void* workspace, size_t workspace_bytes, void* hip_stream);
 
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight
  * serving loops, harnesses that forbid allocation): sim_critic_values without a workspace.

@@ -87,7 +87,7 @@ EXPORTS = ["sim_create", "sim_workspace_bytes", "sim_dims", "sim_forward_window"
            "sim_tune", "sim_probe_fma_bytes", "sim_probe_fma", "sim_probe_copy", "sim_adam_step",
            "sim_soft_update", "sim_td_lambda", "sim_critic_workspace_bytes", "sim_critic_values",
            "sim_critic_fit", "sim_obs_stats_update", "sim_abi_layout", "sim_critic_values_noalloc",
-           "sim_critic_values_ln",
+           "sim_critic_values_ln", "sim_obs_stats_workspace_bytes", "sim_obs_stats_update_ws",
            "sim_phase_profile"]
 MAX_GROUP = 6
 
@@ -155,6 +155,10 @@ def lib():
         L.sim_critic_fit.restype = _i
         L.sim_obs_stats_update.argtypes = [_p, ctypes.c_long, _i, _d, _p, _p, _p, _d, _i, _p]
         L.sim_obs_stats_update.restype = _i
+        L.sim_obs_stats_workspace_bytes.argtypes = [ctypes.c_long, _i]
+        L.sim_obs_stats_workspace_bytes.restype = ctypes.c_size_t
+        L.sim_obs_stats_update_ws.argtypes = [_p, ctypes.c_long, _i, _d, _p, _p, _p, _d, _i, _p, ctypes.c_size_t, _p]
+        L.sim_obs_stats_update_ws.restype = _i
         L.sim_critic_values_noalloc.argtypes = [_p, _p, _i, ctypes.POINTER(_p), ctypes.POINTER(_p), _p, _p, _p, _p]
         L.sim_critic_values_noalloc.restype = _i
         L.sim_abi_layout.argtypes = [_i, _i]
@@ -707,14 +711,18 @@ def td_lambda(rewards, values, gamma=0.99, lam=0.95, done=None):
 
 
 def obs_stats_update(obs, count, mean, var, inv_std, eps=1e-5):
-    """sim_obs_stats_update: merges obs [rows, dim] (device) into the running statistics
+    """sim_obs_stats_update_ws: merges obs [rows, dim] (device) into the running statistics
     (count, mean [dim], var [dim]) in place, writes inv_std = 1 / sqrt(var + eps), and
     returns the new count."""
     obs = obs.reshape(-1, mean.numel())
     assert obs.is_contiguous() and all(x.dtype == obs.dtype and x.is_cuda for x in (mean, var, inv_std))
     rows, dim = obs.shape
-    _check(lib().sim_obs_stats_update(_p(obs.data_ptr()), rows, dim, float(count), _p(mean.data_ptr()),
-                                      _p(var.data_ptr()), _p(inv_std.data_ptr()), float(eps), _prec(obs), _stream()))
+    # scratch from torch's allocator: ordered on the current stream, like the kernels
+    nb = int(lib().sim_obs_stats_workspace_bytes(rows, dim))
+    ws = obs.new_empty(nb // obs.element_size())
+    _check(lib().sim_obs_stats_update_ws(_p(obs.data_ptr()), rows, dim, float(count), _p(mean.data_ptr()),
+                                         _p(var.data_ptr()), _p(inv_std.data_ptr()), float(eps), _prec(obs),
+                                         _p(ws.data_ptr()), nb, _stream()))
     return count + rows
 
 

@@ -1471,8 +1471,21 @@ int sim_probe_copy(const void* src, void* dst, size_t bytes, void* hip_stream, d
 // ======================================================================= learning-episode update
 static int learn_launch(float, const LearnAdamT<float>& A, void* s) { return sim_l32::launch_adam(A, s); }
 static int learn_launch(double, const LearnAdamT<double>& A, void* s) { return sim_l64::launch_adam(A, s); }
-static int soft_launch(float* t, const float* o, long n, double a, void* s) { return sim_l32::launch_soft_update(t, o, n, (float)a, s); }
-static int soft_launch(double* t, const double* o, long n, double a, void* s) { return sim_l64::launch_soft_update(t, o, n, a, s); }
+static int soft_launch(const SoftUpdateT<float>& A, void* s) { return sim_l32::launch_soft_update(A, s); }
+static int soft_launch(const SoftUpdateT<double>& A, void* s) { return sim_l64::launch_soft_update(A, s); }
+template <typename T>
+static int soft_impl(void* const* target, const void* const* online, const size_t* sizes, int n, double alpha, void* s) {
+  SoftUpdateT<T> A;
+  std::memset(&A, 0, sizeof(A));
+  A.n = n;
+  for (int i = 0; i < n; ++i) {
+    A.t[i] = static_cast<T*>(target[i]);
+    A.o[i] = static_cast<const T*>(online[i]);
+    A.size[i] = (long)sizes[i];
+  }
+  A.alpha = (T)alpha;
+  return soft_launch(A, s);
+}
 static int td_launch(const float* r, const float* v, const uint8_t* d, int h, int N, double g, double l, float* out,
                      void* s) {
   return sim_l32::launch_td_lambda(r, v, d, h, N, (float)g, (float)l, out, s);
@@ -1530,13 +1543,8 @@ extern "C" int sim_soft_update(void* const* target, const void* const* online, c
     if (!target[i] || !online[i] || sizes[i] == 0) return fail(SIM_E_ARG, "sim_soft_update: null or empty tensor");
   if (!(alpha >= 0.0 && alpha <= 1.0)) return fail(SIM_E_ARG, "sim_soft_update: alpha outside [0, 1]");
   if (precision != SIM_PREC_FP32 && precision != SIM_PREC_FP64) return fail(SIM_E_ARG, "sim_soft_update: unknown precision");
-  int bad = 0;
-  for (int i = 0; i < n_tensors; ++i) {
-    if (precision == SIM_PREC_FP32)
-      bad |= soft_launch(static_cast<float*>(target[i]), static_cast<const float*>(online[i]), (long)sizes[i], alpha, hip_stream);
-    else
-      bad |= soft_launch(static_cast<double*>(target[i]), static_cast<const double*>(online[i]), (long)sizes[i], alpha, hip_stream);
-  }
+  const int bad = precision == SIM_PREC_FP32 ? soft_impl<float>(target, online, sizes, n_tensors, alpha, hip_stream)
+                                             : soft_impl<double>(target, online, sizes, n_tensors, alpha, hip_stream);
   if (bad) return launch_failed();
   g_err.clear();
   return SIM_OK;
@@ -1562,20 +1570,21 @@ extern "C" int sim_td_lambda(const void* rewards, const void* values, const uint
   return SIM_OK;
 }
 
-extern "C" int sim_obs_stats_update(const void* obs, long rows, int dim, double count, void* mean, void* var,
-                                    void* inv_std, double eps, int precision, void* hip_stream) {
-  if (!obs || !mean || !var || !inv_std || rows < 1 || dim < 1)
-    return fail(SIM_E_ARG, "sim_obs_stats_update: null pointer or empty batch");
-  if (!(count >= 0.0) || !(eps >= 0.0)) return fail(SIM_E_ARG, "sim_obs_stats_update: need count >= 0 and eps >= 0");
+static int obs_stats_checked(const char* fn, const void* obs, long rows, int dim, double count, void* mean, void* var,
+                             void* inv_std, double eps, int precision, void* ws, void* hip_stream) {
+  const std::string f(fn);
+  if (!obs || !mean || !var || !inv_std || rows < 1 || dim < 1) return fail(SIM_E_ARG, f + ": null pointer or empty batch");
+  if (!(count >= 0.0) || !(eps >= 0.0)) return fail(SIM_E_ARG, f + ": need count >= 0 and eps >= 0");
+  double* w = static_cast<double*>(ws);
   int bad;
   if (precision == SIM_PREC_FP32)
     bad = sim_l32::launch_obs_stats(static_cast<const float*>(obs), rows, dim, count, static_cast<float*>(mean),
-                                    static_cast<float*>(var), static_cast<float*>(inv_std), eps, hip_stream);
+                                    static_cast<float*>(var), static_cast<float*>(inv_std), eps, w, hip_stream);
   else if (precision == SIM_PREC_FP64)
     bad = sim_l64::launch_obs_stats(static_cast<const double*>(obs), rows, dim, count, static_cast<double*>(mean),
-                                    static_cast<double*>(var), static_cast<double*>(inv_std), eps, hip_stream);
+                                    static_cast<double*>(var), static_cast<double*>(inv_std), eps, w, hip_stream);
   else
-    return fail(SIM_E_ARG, "sim_obs_stats_update: unknown precision");
+    return fail(SIM_E_ARG, f + ": unknown precision");
   if (bad) return launch_failed();
   g_err.clear();
   return SIM_OK;
@@ -1584,6 +1593,27 @@ extern "C" int sim_obs_stats_update(const void* obs, long rows, int dim, double 
 // workspace of the critic calls: x [rows][od], y [rows], V [rows], H[1..nl-1] [rows][dims],
 // d0 / d1 [rows][max width], split partials, the flat gradient
 #define CRITIC_SPLITS 32
+extern "C" int sim_obs_stats_update(const void* obs, long rows, int dim, double count, void* mean, void* var,
+                                    void* inv_std, double eps, int precision, void* hip_stream) {
+  return obs_stats_checked("sim_obs_stats_update", obs, rows, dim, count, mean, var, inv_std, eps, precision, nullptr,
+                           hip_stream);
+}
+
+extern "C" size_t sim_obs_stats_workspace_bytes(long rows, int dim) {
+  if (rows < 1 || dim < 1) return 0;
+  return (size_t)obs_stats_plan(rows, dim).chunks * 2 * (size_t)dim * sizeof(double);
+}
+
+extern "C" int sim_obs_stats_update_ws(const void* obs, long rows, int dim, double count, void* mean, void* var,
+                                       void* inv_std, double eps, int precision, void* workspace,
+                                       size_t workspace_bytes, void* hip_stream) {
+  const size_t need = sim_obs_stats_workspace_bytes(rows, dim);
+  if (need > 0 && (!workspace || workspace_bytes < need || reinterpret_cast<uintptr_t>(workspace) % sizeof(double) != 0))
+    return fail(SIM_E_WORKSPACE, "sim_obs_stats_update_ws: workspace smaller than sim_obs_stats_workspace_bytes() or misaligned");
+  return obs_stats_checked("sim_obs_stats_update_ws", obs, rows, dim, count, mean, var, inv_std, eps, precision,
+                           need > 0 ? workspace : nullptr, hip_stream);
+}
+
 struct CriticWs {
   size_t x, y, v, h[SIM_MAXL], d0, d1, part, grad, total;
   size_t yn[SIM_MAXL], st, lnpart;   // with layer normalisation

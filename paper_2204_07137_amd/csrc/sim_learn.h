@@ -28,29 +28,57 @@ __global__ void k_adam_multi(LearnAdamT<real> A, long total) {
   A.p[t][i - base] -= A.lr * (m / A.bc1) / (m_sqrt(v / A.bc2) + A.eps);
 }
 
-// target <- alpha target + (1 - alpha) online
-__global__ void k_soft_update(real* __restrict__ t, const real* __restrict__ o, long n, real alpha) {
+// target <- alpha target + (1 - alpha) online over every tensor of a list in one launch (a
+// launch per tensor spent 20 us on the six tensors of a 27 k-parameter critic); element i of
+// the list belongs to the tensor whose range holds it
+__global__ void k_soft_update(SoftUpdateT<real> A, long total) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) t[i] = alpha * t[i] + (RL(1.0) - alpha) * o[i];
+  if (i >= total) return;
+  real* t = A.t[0] + i;
+  const real* o = A.o[0] + i;
+  long base = 0;
+#pragma unroll
+  for (int k = 1; k < SIM_MAX_TENSORS; ++k) {
+    base += A.size[k - 1];
+    if (k < A.n && i >= base) {
+      t = A.t[k] + (i - base);
+      o = A.o[k] + (i - base);
+    }
+  }
+  *t = A.alpha * *t + (RL(1.0) - A.alpha) * *o;
 }
 
 // TD-lambda estimates, one thread per env, by the backward recursion
 // G_t = r_t + gamma ((1 - lambda) V_{t+1} + lambda G_{t+1}) from G_h = V_h, which equals the
 // lambda-weighted average of the k-step returns of the definition.
 // r [h][N], v [h+1][N] (values of s_0 .. s_h; s_0's is not used), out [h][N]
+#define TD_BATCH 8
 __global__ void k_td_lambda(const real* __restrict__ r, const real* __restrict__ v, const uint8_t* __restrict__ done,
                             int h, int N, real gamma, real lam, real* __restrict__ out) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= N) return;
   real G = v[(size_t)h * N + e];
-  for (int t = h - 1; t >= 0; --t) {
-    // a frame that ended in termination returns its reward alone: every k-step return from
-    // it stops there and the fallen state has no value (s_{t+1} is already the reset state)
-    if (done && done[(size_t)t * N + e])
-      G = r[(size_t)t * N + e];
-    else
-      G = r[(size_t)t * N + e] + gamma * ((RL(1.0) - lam) * v[(size_t)(t + 1) * N + e] + lam * G);
-    out[(size_t)t * N + e] = G;
+  // The recursion is serial but its inputs are not: TD_BATCH frames are requested at a time, so
+  // a thread waits for one memory latency per batch instead of one per frame.
+  for (int t1 = h - 1; t1 >= 0; t1 -= TD_BATCH) {
+    real rt[TD_BATCH], vt[TD_BATCH];
+    bool dn[TD_BATCH];
+#pragma unroll
+    for (int u = 0; u < TD_BATCH; ++u) {
+      const size_t t = (size_t)(t1 - u > 0 ? t1 - u : 0);
+      rt[u] = r[t * N + e];
+      vt[u] = v[(t + 1) * N + e];
+      dn[u] = done && done[t * N + e];
+    }
+#pragma unroll
+    for (int u = 0; u < TD_BATCH; ++u) {
+      if (t1 - u < 0) break;
+      // a frame that ended in termination returns its reward alone: every k-step return from
+      // it stops there and the fallen state has no value (s_{t+1} is already the reset state)
+      if (dn[u]) G = rt[u];
+      else G = rt[u] + gamma * ((RL(1.0) - lam) * vt[u] + lam * G);
+      out[(size_t)(t1 - u) * N + e] = G;
+    }
   }
 }
 
@@ -74,9 +102,23 @@ __global__ void k_gather_rows(const real* __restrict__ obs, const real* __restri
 // Chan, Golub and LeVeque: with the batch's own mean m_b and sum of squared deviations
 // M2_b, delta = m_b - mean, n = count + rows,
 //   mean' = mean + delta rows / n,   var' = (var count + M2_b + delta^2 count rows / n) / n,
-// and inv_std = 1 / sqrt(var' + eps).  A block owns 64 columns; its 16 row groups read
-// consecutive columns of a row (coalesced) and are summed in a fixed order, in FP64.  Each
-// thread keeps eight independent partial sums so that eight loads are in flight at once.
+// and inv_std = 1 / sqrt(var' + eps).  All sums in FP64, in a fixed order.
+__device__ __forceinline__ void os_merge(real* mean, real* var, real* inv_std, int c, double count, double rows,
+                                         double bm, double m2b, double eps) {
+  const double n = count + rows;
+  const double m0 = count > 0.0 ? (double)mean[c] : 0.0;
+  const double v0 = count > 0.0 ? (double)var[c] : 0.0;
+  const double delta = bm - m0;
+  const double mn = m0 + delta * (rows / n);
+  const double vn = (v0 * count + m2b + delta * delta * (count * rows / n)) / n;
+  mean[c] = (real)mn;
+  var[c] = (real)vn;
+  inv_std[c] = (real)(1.0 / sqrt(vn + eps));
+}
+
+// Without a workspace: a block owns 64 columns; its 16 row groups read consecutive columns of a
+// row (coalesced), twice (the mean, then the deviations).  Each thread keeps eight independent
+// partial sums so that eight loads are in flight at once.
 #define OS_COLS 64
 #define OS_GROUPS 16
 #define OS_UNROLL 8
@@ -95,43 +137,133 @@ __device__ __forceinline__ double os_column_sum(const real* __restrict__ x, long
   for (; r < rows; r += OS_GROUPS) p[0] += f((double)x[r * od + c]);
   return ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
 }
+// the row groups' sums of a column, added in group order; every thread of the column gets it
+__device__ __forceinline__ double os_group_sum(double (*red)[OS_COLS], double s, int cl, int grp) {
+  __syncthreads();
+  red[grp][cl] = s;
+  __syncthreads();
+  double t = 0.0;
+  for (int g = 0; g < OS_GROUPS; ++g) t += red[g][cl];
+  return t;
+}
 __global__ __launch_bounds__(OS_COLS * OS_GROUPS) void k_obs_stats(const real* __restrict__ x, long rows, int od,
                                                                     double count, real* __restrict__ mean,
                                                                     real* __restrict__ var, real* __restrict__ inv_std,
                                                                     double eps) {
   __shared__ double red[OS_GROUPS][OS_COLS];
-  __shared__ double bmean[OS_COLS];
   const int cl = threadIdx.x % OS_COLS, grp = threadIdx.x / OS_COLS;
   const int c = blockIdx.x * OS_COLS + cl;
   const bool ok = c < od;
-  double s = 0.0;
+  double s = 0.0, q = 0.0;
   if (ok) s = os_column_sum(x, rows, od, c, grp, [](double v) { return v; });
+  const double bm = os_group_sum(red, s, cl, grp) / (double)rows;
+  if (ok) q = os_column_sum(x, rows, od, c, grp, [bm](double v) { const double d = v - bm; return d * d; });
+  const double m2b = os_group_sum(red, q, cl, grp);
+  if (grp == 0 && ok) os_merge(mean, var, inv_std, c, count, (double)rows, bm, m2b, eps);
+}
+
+// With a workspace: the rows are read once, by as many blocks as there are chunks of them.  The
+// column blocks above leave 2 of 256 CUs working on a 76-column batch: 32768 rows of it take
+// 221 us there and 12.4 us here (10 MB read, two launches), 1024 rows 8.1 and 8.9 us, 2048 rows
+// 13.2 and 9.0 us.  A block of OSP_THREADS threads
+// takes OSP_UNROLL rows for each of its row groups and w consecutive columns, so that its threads
+// read consecutive words, holds them in registers, and leaves its rows' column sums and sums of
+// squared deviations from its own column means; k_obs_stats_merge joins the chunks:
+//   M2 = sum_b (M2_b + n_b (mean_b - mean)^2).
+#define OSP_THREADS SIM_OSP_THREADS
+#define OSP_UNROLL SIM_OSP_UNROLL
+__global__ __launch_bounds__(OSP_THREADS) void k_obs_stats_part(const real* __restrict__ x, long rows, int od, int w,
+                                                                 int groups, double* __restrict__ part) {
+  __shared__ double red[OSP_THREADS];
+  const int tid = threadIdx.x, grp = tid / w, cl = tid % w;
+  const int c = blockIdx.y * w + cl;
+  const bool on = grp < groups && c < od;
+  const long r0 = (long)blockIdx.x * groups * OSP_UNROLL;
+  const long nb = min((long)groups * OSP_UNROLL, rows - r0);
+  real v[OSP_UNROLL];
+  double s = 0.0;
+#pragma unroll
+  for (int u = 0; u < OSP_UNROLL; ++u) {
+    const long r = r0 + (long)u * groups + grp;
+    v[u] = (on && r < rows) ? x[r * od + c] : RL(0.0);
+  }
+#pragma unroll
+  for (int u = 0; u < OSP_UNROLL; ++u) s += (double)v[u];
+  red[tid] = s;
+  __syncthreads();
+  double sum = 0.0;
+  for (int g = 0; g < groups; ++g) sum += red[g * w + cl];
+  const double bm = sum / (double)nb;
+  double q = 0.0;
+#pragma unroll
+  for (int u = 0; u < OSP_UNROLL; ++u) {
+    const double d = (double)v[u] - bm;
+    if (r0 + (long)u * groups + grp < rows) q += d * d;
+  }
+  __syncthreads();
+  red[tid] = q;
+  __syncthreads();
+  if (grp == 0 && on) {
+    double m2 = 0.0;
+    for (int g = 0; g < groups; ++g) m2 += red[g * w + cl];
+    part[(size_t)blockIdx.x * od + c] = sum;
+    part[((size_t)gridDim.x + blockIdx.x) * od + c] = m2;
+  }
+}
+// A block joins the chunks of 16 columns, 64 groups of chunks side by side (a few chunks each:
+// the join is a chain of memory latencies, 18 us with the column blocks' 64 x 16 split).
+#define OSM_COLS 16
+#define OSM_GROUPS 64
+__device__ __forceinline__ double osm_sum(double (*red)[OSM_COLS], double s, int cl, int grp) {
+  __syncthreads();
   red[grp][cl] = s;
   __syncthreads();
-  if (grp == 0) {
-    double t = 0.0;
-    for (int g = 0; g < OS_GROUPS; ++g) t += red[g][cl];
-    bmean[cl] = t / (double)rows;
+  for (int w = OSM_GROUPS / 2; w > 0; w >>= 1) {
+    if (grp < w) red[grp][cl] += red[grp + w][cl];
+    __syncthreads();
   }
-  __syncthreads();
-  const double bm = bmean[cl];
-  double q = 0.0;
-  if (ok) q = os_column_sum(x, rows, od, c, grp, [bm](double v) { const double d = v - bm; return d * d; });
-  red[grp][cl] = q;
-  __syncthreads();
-  if (grp == 0 && ok) {
-    double m2b = 0.0;
-    for (int g = 0; g < OS_GROUPS; ++g) m2b += red[g][cl];
-    const double n = count + (double)rows;
-    const double m0 = count > 0.0 ? (double)mean[c] : 0.0;
-    const double v0 = count > 0.0 ? (double)var[c] : 0.0;
-    const double delta = bm - m0;
-    const double mn = m0 + delta * ((double)rows / n);
-    const double vn = (v0 * count + m2b + delta * delta * (count * (double)rows / n)) / n;
-    mean[c] = (real)mn;
-    var[c] = (real)vn;
-    inv_std[c] = (real)(1.0 / sqrt(vn + eps));
+  return red[0][cl];
+}
+__global__ __launch_bounds__(OSM_COLS * OSM_GROUPS) void k_obs_stats_merge(const double* __restrict__ part, int chunks,
+                                                                            long chunk_rows, long rows, int od,
+                                                                            double count, real* __restrict__ mean,
+                                                                            real* __restrict__ var,
+                                                                            real* __restrict__ inv_std, double eps) {
+  __shared__ double red[OSM_GROUPS][OSM_COLS];
+  const int cl = threadIdx.x % OSM_COLS, grp = threadIdx.x / OSM_COLS;
+  const int c = blockIdx.x * OSM_COLS + cl;
+  const bool ok = c < od;
+  const double* sp = part + (ok ? c : 0);
+  const double* mp = sp + (size_t)chunks * od;
+  double s = 0.0, q = 0.0;
+  for (int b0 = grp; b0 < chunks; b0 += OSM_GROUPS * 8) {
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = (b0 + u * OSM_GROUPS < chunks) ? sp[(size_t)(b0 + u * OSM_GROUPS) * od] : 0.0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += v[u];
   }
+  const double bm = osm_sum(red, s, cl, grp) / (double)rows;
+  for (int b0 = grp; b0 < chunks; b0 += OSM_GROUPS * 4) {
+    double v[4], m2[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const bool in = b0 + u * OSM_GROUPS < chunks;
+      v[u] = in ? sp[(size_t)(b0 + u * OSM_GROUPS) * od] : 0.0;
+      m2[u] = in ? mp[(size_t)(b0 + u * OSM_GROUPS) * od] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const long b = b0 + u * OSM_GROUPS;
+      if (b < chunks) {
+        const double nb = (double)min(chunk_rows, rows - b * chunk_rows);
+        const double d = v[u] / nb - bm;
+        q += m2[u] + nb * d * d;
+      }
+    }
+  }
+  const double m2b = osm_sum(red, q, cl, grp);
+  if (grp == 0 && ok) os_merge(mean, var, inv_std, c, count, (double)rows, bm, m2b, eps);
 }
 
 // output adjoint of the mean squared error (1/B) sum (V - y)^2
@@ -169,9 +301,10 @@ int launch_adam(const LearnAdamT<real>& A, void* stream) {
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-int launch_soft_update(real* t, const real* o, long n, real alpha, void* stream) {
-  hipLaunchKernelGGL(k_soft_update, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, (hipStream_t)stream, t, o, n,
-                     alpha);
+int launch_soft_update(const SoftUpdateT<real>& A, void* stream) {
+  long total = 0;
+  for (int i = 0; i < A.n; ++i) total += A.size[i];
+  hipLaunchKernelGGL(k_soft_update, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, (hipStream_t)stream, A, total);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -183,9 +316,18 @@ int launch_td_lambda(const real* r, const real* v, const uint8_t* done, int h, i
 }
 
 int launch_obs_stats(const real* x, long rows, int od, double count, real* mean, real* var, real* inv_std,
-                     double eps, void* stream) {
-  hipLaunchKernelGGL(k_obs_stats, dim3((unsigned)((od + OS_COLS - 1) / OS_COLS)), dim3(OS_COLS * OS_GROUPS), 0,
-                     (hipStream_t)stream, x, rows, od, count, mean, var, inv_std, eps);
+                     double eps, double* ws, void* stream) {
+  hipStream_t s = (hipStream_t)stream;
+  const dim3 cols((unsigned)((od + OS_COLS - 1) / OS_COLS));
+  if (!ws) {
+    hipLaunchKernelGGL(k_obs_stats, cols, dim3(OS_COLS * OS_GROUPS), 0, s, x, rows, od, count, mean, var, inv_std, eps);
+  } else {
+    const ObsStatsPlan P = obs_stats_plan(rows, od);
+    hipLaunchKernelGGL(k_obs_stats_part, dim3((unsigned)P.chunks, (unsigned)((od + P.width - 1) / P.width)),
+                       dim3(OSP_THREADS), 0, s, x, rows, od, P.width, P.groups, ws);
+    hipLaunchKernelGGL(k_obs_stats_merge, dim3((unsigned)((od + OSM_COLS - 1) / OSM_COLS)), dim3(OSM_COLS * OSM_GROUPS), 0, s, ws, (int)P.chunks, P.chunk_rows, rows,
+                       od, count, mean, var, inv_std, eps);
+  }
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

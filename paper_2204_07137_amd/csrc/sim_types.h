@@ -278,8 +278,35 @@ struct LearnAdamT {
   T lr, b1, b2, eps, bc1, bc2;   // bc = 1 - beta^step (bias corrections)
 };
 
-// Critic fit over shuffled minibatches (the layer gradients run through G, whose x0 / M are
-// set per minibatch and whose out is the flat gradient buffer).
+// target <- alpha target + (1 - alpha) online over a list of tensors
+template <typename T>
+struct SoftUpdateT {
+  int n;
+  T* t[SIM_MAX_TENSORS];
+  const T* o[SIM_MAX_TENSORS];
+  long size[SIM_MAX_TENSORS];
+  T alpha;
+};
+
+// How the observation statistics split a batch over blocks: `groups` row groups of `width`
+// columns per block of SIM_OSP_THREADS threads, SIM_OSP_UNROLL rows per group.  Below
+// SIM_OSP_ROWS rows the single launch of the column blocks is the faster one (chunks = 0).
+#define SIM_OSP_THREADS 512
+#define SIM_OSP_UNROLL 16
+#define SIM_OSP_ROWS 1024
+struct ObsStatsPlan { int width, groups; long chunk_rows, chunks; };
+static inline ObsStatsPlan obs_stats_plan(long rows, int od) {
+  ObsStatsPlan P;
+  const int tiles = (od + SIM_OSP_THREADS - 1) / SIM_OSP_THREADS;
+  P.width = (od + tiles - 1) / tiles;
+  P.groups = SIM_OSP_THREADS / P.width;
+  P.chunk_rows = (long)P.groups * SIM_OSP_UNROLL;
+  P.chunks = rows < SIM_OSP_ROWS ? 0 : (rows + P.chunk_rows - 1) / P.chunk_rows;
+  return P;
+}
+
+// Critic fit over shuffled minibatches (the layer gradients run through G, whose M is set per
+// minibatch).
 template <typename T>
 struct CriticFitT {
   ThetaArgsT<T> G;      // layer-gradient pass
@@ -320,11 +347,11 @@ SIM_DECLARE_LAUNCHERS(sim_f64, double)
 #define SIM_DECLARE_LEARN(NS, T)                                                           \
   namespace NS {                                                                           \
   int launch_adam(const LearnAdamT<T>& A, void* stream);                                   \
-  int launch_soft_update(T* t, const T* o, long n, T alpha, void* stream);                 \
+  int launch_soft_update(const SoftUpdateT<T>& A, void* stream);                           \
   int launch_td_lambda(const T* r, const T* v, const uint8_t* d, int h, int N, T g, T l, T* out, void* s); \
   int launch_critic_values(const ThetaArgsT<T>& A, T* out, void* stream);                  \
   int launch_obs_stats(const T* x, long rows, int od, double count, T* mean, T* var, T* inv_std, double eps,   \
-                       void* stream);                                                      \
+                       double* ws, void* stream);                                          \
   int launch_critic_fit(const CriticFitT<T>& F, void* stream);                             \
   }
 SIM_DECLARE_LEARN(sim_l32, float)

@@ -1,0 +1,55 @@
+"""Observation statistics around the rule that picks the chunked kernels, TD-lambda around its
+batch of frames, and the soft update of a full list of tensors, against the FP64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2204_07137_amd as P
+from oracle import learn as OL
+
+pytestmark = pytest.mark.gpu
+
+
+def rel(x, y):
+    x, y = x.double().cpu().reshape(-1), torch.as_tensor(y, dtype=torch.float64).reshape(-1)
+    return float((x - y).norm() / y.norm().clamp_min(1e-300))
+
+
+# FP32: the sums are FP64, only the results are rounded
+@pytest.mark.parametrize("dt,tol", [(torch.float64, 1e-12), (torch.float32, 1e-6)])
+@pytest.mark.parametrize("dim", [1, 5, 76, 257, 513])
+def test_obs_stats_match_oracle(dim, dt, tol):
+    for rows in (1, 1023, 1024, 1025, 9001):
+        for count in (0.0, 12345.0):
+            print(f"[update] stats rows={rows} dim={dim} count={count} {dt}", flush=True)
+            rng = np.random.default_rng(rows + dim)
+            x = torch.as_tensor((3.0 + rng.normal(size=(rows, dim))).astype(np.float32)).to("cuda", dt)
+            mean = torch.as_tensor(rng.normal(size=dim).astype(np.float32)).to("cuda", dt)
+            var = torch.as_tensor(rng.uniform(0.5, 2.0, dim).astype(np.float32)).to("cuda", dt)
+            inv = torch.empty_like(mean)
+            n, m, v, s = OL.obs_stats_update(x.cpu(), count, mean.cpu(), var.cpu(), 1e-5)
+            assert P.obs_stats_update(x, count, mean, var, inv) == n
+            assert rel(mean, m) < tol and rel(inv, s) < tol
+            assert float((var.double().cpu() - v).abs().max()) < tol * (1.0 + float(v.max()))
+
+
+@pytest.mark.parametrize("h", [1, 7, 8, 9, 17])
+def test_td_lambda_matches_oracle(h):
+    rng = np.random.default_rng(h)
+    for N in (1, 65):
+        r, v = (torch.as_tensor(rng.normal(size=s)).cuda() for s in ((h, N), (h + 1, N)))
+        for done in (None, torch.as_tensor(rng.uniform(size=(h, N)) < 0.3).to(torch.uint8).cuda()):
+            got = P.td_lambda(r, v, 0.99, 0.95, done=done)
+            ref = OL.td_lambda(r.cpu(), v.cpu(), 0.99, 0.95, None if done is None else done.cpu())
+            assert rel(got, ref) < 1e-12
+
+
+@pytest.mark.parametrize("n", [1, 6, 16])
+def test_soft_update_lists(n):
+    g = torch.Generator().manual_seed(n)
+    t = [torch.randn(1 + 37 * i, generator=g, dtype=torch.float64).cuda() for i in range(n)]
+    o = [torch.randn(x.shape, generator=g, dtype=torch.float64).cuda() for x in t]
+    want = [0.995 * a.cpu() + (1.0 - 0.995) * b.cpu() for a, b in zip(t, o)]
+    P.soft_update(t, o, 0.995)
+    for a, b in zip(t, want):
+        assert rel(a, b) < 1e-15
