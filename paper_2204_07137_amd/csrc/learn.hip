@@ -3,6 +3,7 @@
 // row-contraction GEMMs.
 #include <hip/hip_runtime.h>
 #include <math.h>
+#include <type_traits>
 #include "sim_types.h"
 
 namespace sim_l32 {

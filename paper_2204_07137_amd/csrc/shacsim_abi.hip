@@ -89,7 +89,7 @@ struct SimHandle {
   // policy-gradient scratch: two layer-adjoint buffers, split partials (the hidden
   // activations are the window's own, at off_hid)
   size_t off_th_d0 = 0, off_th_d1 = 0, off_th_part = 0;
-  int th_splits = 0;
+  long th_part_cap = 0;   // values of the split partials
   int n_ckpt = 0;
   int device = -1;
   uint32_t magic = kMagic;
@@ -688,13 +688,14 @@ extern "C" int sim_create(const SimModelDesc* md, const SimOptions* opt, SimHand
       maxpart = std::max(maxpart, (size_t)opt->actor_dims[l + 1] * (opt->actor_dims[l] + 1));
     }
     // row chunks of at least 512 rows, at most 64 of them
-    h->th_splits = (int)std::min<size_t>(64, std::max<size_t>(1, rows / 512));
+    const size_t th_splits = std::min<size_t>(64, std::max<size_t>(1, rows / 512));
+    h->th_part_cap = (long)(th_splits * maxpart);
     h->off_th_d0 = off;
     off = align256(off + e * rows * maxw);
     h->off_th_d1 = off;
     off = align256(off + e * rows * maxw);
     h->off_th_part = off;
-    off = align256(off + e * (size_t)h->th_splits * maxpart);
+    off = align256(off + e * th_splits * maxpart);
     if (opt->layer_norm) {
       // the normalised hidden layers of every row and the gain / bias partials
       size_t hw = 0;
@@ -886,7 +887,6 @@ static void build_theta_args(SimHandle* h, const SimAdjointIO* io, ThetaArgsT<T>
   P.M = o.n_envs * o.horizon;
   P.nl = o.actor_layers;
   for (int l = 0; l <= o.actor_layers; ++l) P.dims[l] = o.actor_dims[l];
-  P.splits = h->th_splits;
   long off = 0;
   for (int l = 0; l < o.actor_layers; ++l) {
     P.W[l] = static_cast<const T*>(io->actor_w[l]);
@@ -913,6 +913,7 @@ static void build_theta_args(SimHandle* h, const SimAdjointIO* io, ThetaArgsT<T>
   P.d0 = reinterpret_cast<T*>(ws + h->off_th_d0);
   P.d1 = reinterpret_cast<T*>(ws + h->off_th_d1);
   P.part = reinterpret_cast<T*>(ws + h->off_th_part);
+  P.part_cap = h->th_part_cap;
   P.out = static_cast<T*>(io->dL_dtheta);
   // the gradient is taken at the activations the window itself computed (stored by the
   // forward), rows (t, env) as the observations' (handles with BF16 MLPs have no dL/dtheta,
@@ -937,7 +938,9 @@ static void build_theta_args(SimHandle* h, const SimAdjointIO* io, ThetaArgsT<T>
         yo += (long)P.M * o.actor_dims[l];
       }
       P.lnpart = reinterpret_cast<T*>(ws + h->off_th_lnp);
-      P.ln_blocks = SIM_LN_BLOCKS;
+      int maxw = 0;
+      for (int l = 0; l < o.actor_layers; ++l) maxw = std::max(maxw, o.actor_dims[l + 1]);
+      P.lnpart_cap = (long)SIM_LN_BLOCKS * 2 * maxw;
     }
   }
   P.mtu = (h->m64.task == TASK_MTU) ? 1 : 0;
@@ -1590,9 +1593,6 @@ static int obs_stats_checked(const char* fn, const void* obs, long rows, int dim
   return SIM_OK;
 }
 
-// workspace of the critic calls: x [rows][od], y [rows], V [rows], H[1..nl-1] [rows][dims],
-// d0 / d1 [rows][max width], split partials, the flat gradient
-#define CRITIC_SPLITS 32
 extern "C" int sim_obs_stats_update(const void* obs, long rows, int dim, double count, void* mean, void* var,
                                     void* inv_std, double eps, int precision, void* hip_stream) {
   return obs_stats_checked("sim_obs_stats_update", obs, rows, dim, count, mean, var, inv_std, eps, precision, nullptr,
@@ -1614,8 +1614,13 @@ extern "C" int sim_obs_stats_update_ws(const void* obs, long rows, int dim, doub
                            need > 0 ? workspace : nullptr, hip_stream);
 }
 
+// workspace of the critic calls: x [rows][od], y [rows], V [rows], H[1..nl-1] [rows][dims],
+// d0 / d1 [rows][max width], split partials, the flat gradient
+#define CRITIC_SPLITS 32
 struct CriticWs {
   size_t x, y, v, h[SIM_MAXL], d0, d1, part, grad, total;
+  size_t part_n;   // values of the split partials
+  int maxd;        // widest layer
   size_t yn[SIM_MAXL], st, lnpart;   // with layer normalisation
 };
 static CriticWs critic_ws(const SimOptions& o, int rows, size_t e) {
@@ -1638,6 +1643,9 @@ static CriticWs critic_ws(const SimOptions& o, int rows, size_t e) {
   w.d1 = off; off = align256(off + (size_t)rows * maxd * e);
   w.part = off; off = align256(off + (size_t)CRITIC_SPLITS * maxpart * e);
   w.grad = off; off = align256(off + nparams * e);
+  // the gradient buffer serves a single chunk's gradient only, so more chunks run on into it
+  w.part_n = (w.grad - w.part) / e + nparams;
+  w.maxd = maxd;
   if (o.layer_norm && L > 1) {
     // the normalised hidden layers, their per-row statistics, the gain / bias partials
     for (int l = 1; l < L; ++l) { w.yn[l] = off; off = align256(off + (size_t)rows * o.critic_dims[l] * e); }
@@ -1662,7 +1670,6 @@ static void critic_theta_args(const SimHandle* h, const CriticWs& w, char* ws, c
   P.M = rows;
   P.nl = o.critic_layers;
   for (int l = 0; l <= o.critic_layers; ++l) P.dims[l] = o.critic_dims[l];
-  P.splits = CRITIC_SPLITS;
   const bool ln = o.layer_norm && o.critic_layers > 1;
   long off = 0;
   for (int l = 0; l < o.critic_layers; ++l) {
@@ -1690,11 +1697,12 @@ static void critic_theta_args(const SimHandle* h, const CriticWs& w, char* ws, c
     P.ldst = 2 * (o.critic_layers - 1);
     for (int l = 1; l < o.critic_layers; ++l) P.Y[l] = reinterpret_cast<T*>(ws + w.yn[l]);
     P.lnpart = reinterpret_cast<T*>(ws + w.lnpart);
-    P.ln_blocks = SIM_LN_BLOCKS;
+    P.lnpart_cap = (long)SIM_LN_BLOCKS * 2 * w.maxd;
   }
   P.d0 = reinterpret_cast<T*>(ws + w.d0);
   P.d1 = reinterpret_cast<T*>(ws + w.d1);
   P.part = reinterpret_cast<T*>(ws + w.part);
+  P.part_cap = (long)w.part_n;
   P.out = reinterpret_cast<T*>(ws + w.grad);
 }
 
@@ -1839,6 +1847,8 @@ static int critic_fit_impl(SimHandle* h, const SimCriticFitIO* io, void* stream)
   F.x = reinterpret_cast<T*>(ws + w.x);
   F.y = reinterpret_cast<T*>(ws + w.y);
   F.vbuf = reinterpret_cast<T*>(ws + w.v);
+  F.scratch = F.vbuf;
+  F.scratch_cap = (long)((w.total - w.v) / sizeof(T));
   for (int l = 0; l < h->opt.critic_layers; ++l) {
     F.W[l] = static_cast<T*>(io->critic_w[l]);
     F.bvec[l] = static_cast<T*>(io->critic_b[l]);

@@ -7,25 +7,11 @@
 // Included inside a namespace with `real` defined as float or double, after sim_math.h and
 // sim_gemm.h.
 
-// Adam (Kingma and Ba): m = b1 m + (1 - b1) g, v = b2 v + (1 - b2) g^2,
-// p -= lr (m / bc1) / (sqrt(v / bc2) + eps) with bc = 1 - b^t, over every tensor of a list in
-// one launch: the gradient and moments are flat with the tensors in list order, and element i
-// belongs to the tensor whose range holds it
+// one Adam step (adam_element) over every tensor of a list in one launch
 __global__ void k_adam_multi(LearnAdamT<real> A, long total) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= total) return;
-  int t = 0;
-  long base = 0;
-  while (t + 1 < A.n && i >= base + A.size[t]) {
-    base += A.size[t];
-    ++t;
-  }
-  const real gi = A.g[i];
-  const real m = A.b1 * A.m[i] + (RL(1.0) - A.b1) * gi;
-  const real v = A.b2 * A.v[i] + (RL(1.0) - A.b2) * gi * gi;
-  A.m[i] = m;
-  A.v[i] = v;
-  A.p[t][i - base] -= A.lr * (m / A.bc1) / (m_sqrt(v / A.bc2) + A.eps);
+  adam_element(A, i, A.g[i]);
 }
 
 // target <- alpha target + (1 - alpha) online over every tensor of a list in one launch (a
@@ -80,21 +66,6 @@ __global__ void k_td_lambda(const real* __restrict__ r, const real* __restrict__
       out[(size_t)(t1 - u) * N + e] = G;
     }
   }
-}
-
-// minibatch rows: x[b] = obs[perm[b]], y[b] = targets[perm[b]]
-// (normalised with the running statistics when given: x = (o - mean) * inv_std)
-__global__ void k_gather_rows(const real* __restrict__ obs, const real* __restrict__ tgt, const int* __restrict__ perm,
-                              int B, int od, const real* __restrict__ mean, const real* __restrict__ inv_std,
-                              real* __restrict__ x, real* __restrict__ y) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (long)B * od) return;
-  const int b = (int)(i / od), c = (int)(i % od);
-  const int r = perm[b];
-  real v = obs[(long)r * od + c];
-  if (mean) v = (v - mean[c]) * inv_std[c];
-  x[i] = v;
-  if (c == 0) y[b] = tgt[r];
 }
 
 // Running observation statistics (Sec. 3.3): merges a batch of rows into the count, mean
@@ -266,30 +237,6 @@ __global__ __launch_bounds__(OSM_COLS * OSM_GROUPS) void k_obs_stats_merge(const
   if (grp == 0 && ok) os_merge(mean, var, inv_std, c, count, (double)rows, bm, m2b, eps);
 }
 
-// output adjoint of the mean squared error (1/B) sum (V - y)^2
-__global__ void k_mse_seed(const real* __restrict__ V, const real* __restrict__ y, int B, real* __restrict__ d) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < B) d[i] = RL(2.0) / (real)B * (V[i] - y[i]);
-}
-
-// the minibatch's mean squared error before the step, by a fixed-order tree (one block)
-__global__ __launch_bounds__(256) void k_mse_loss(const real* __restrict__ V, const real* __restrict__ y, int B,
-                                                  real* __restrict__ out) {
-  __shared__ real part[256];
-  real s = RL(0.0);
-  for (int i = threadIdx.x; i < B; i += 256) {
-    const real d = V[i] - y[i];
-    s += d * d;
-  }
-  part[threadIdx.x] = s;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) *out = part[0] / (real)B;
-}
-
 static void launch_adam_multi(const LearnAdamT<real>& A, hipStream_t s) {
   long total = 0;
   for (int i = 0; i < A.n; ++i) total += A.size[i];
@@ -332,56 +279,119 @@ int launch_obs_stats(const real* x, long rows, int od, double count, real* mean,
 }
 
 int launch_critic_values(const ThetaArgsT<real>& T, real* out, void* stream) {
-  hipStream_t s = (hipStream_t)stream;
-  theta_hidden(T, s);
-  theta_output(T, out, s);
+  RowsArgs R = {};
+  R.V = out;
+  if (launch_rows<ROWS_VALUES>(R, T, nullptr, nullptr, (hipStream_t)stream)) return -1;
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-// n_iter passes over the rows in the order of perm[it], n_mb minibatches each; every
-// minibatch: gather, forward, MSE seed, layer gradients, one Adam step of the critic
+template <int RT, bool LN>
+static int launch_fit_as(const FitArgs& g, int tiles, size_t lds, hipStream_t s) {
+  hipLaunchKernelGGL((k_mlp_fit<RT, LN>), dim3(tiles), dim3(FIT_WAVES * SIM_WAVE), lds, s, g);
+  return 0;
+}
+
+// Whether a minibatch of M rows runs as k_mlp_fit with rt x 16 rows a block: the tile's layers
+// within 52 KB of LDS (three blocks a CU), the tiles' gradients within the scratch, and at most
+// FIT_PARAMS_PER_ROW gradient values written per row (beyond that the gradients are more traffic
+// than the layer inputs and adjoints that k_mlp_rows and k_mlp_wgrad exchange).
+#define FIT_PARAMS_PER_ROW 2048
+static bool fit_plan(const CriticFitT<real>& F, int M, FitArgs& g, int& rt, size_t& lds) {
+  const ThetaArgsT<real>& T = F.G;
+  const long np = mlp_params(T);
+  auto ld = [&](int l) { return l < T.nl ? mlp_pad16(T.dims[l]) + 4 : 0; };
+  g.ld0 = ld(0); g.ld1 = ld(1); g.ld2 = ld(2);
+  for (rt = M >= 32 * MR_CUS ? 2 : 1; rt >= 1; --rt) {
+    const int R = 16 * rt, copies = T.ln ? 2 : 1;
+    g.p1 = R * g.ld0;
+    g.e1 = g.p1 + R * g.ld1;
+    g.p2 = g.p1 + copies * R * g.ld1;
+    g.e2 = g.p2 + R * g.ld2;
+    g.pd = g.p2 + copies * R * g.ld2;
+    lds = (size_t)(g.pd + R * 20) * sizeof(real);
+    if (lds <= 53248 && np <= (long)FIT_PARAMS_PER_ROW * R && (long)((M + R - 1) / R) * np <= F.scratch_cap) return true;
+  }
+  return false;
+}
+
+// n_iter passes over the rows in the order of perm[it], n_mb minibatches each.  A minibatch is
+// two launches: the tiles' gradients, and their sum with the Adam step; larger networks take
+// three (the rows pass, every layer's weight gradient, the sum with the Adam step).
 int launch_critic_fit(const CriticFitT<real>& F, void* stream) {
   hipStream_t s = (hipStream_t)stream;
   ThetaArgsT<real> T = F.G;
+  T.x0 = F.obs;
+  T.x_shift = F.obs_mean;
+  T.x_scale = F.obs_inv_std;
+  ReduceArgs Q = {};
+  Q.fit = 1;
+  Q.loss_part = F.y;
+  LearnAdamT<real> A = {};
+  // the flat gradient holds W_0, b_0, W_1, ... in order; with layer normalisation a hidden
+  // layer's gain and bias follow its W, b
+  for (int l = 0; l < T.nl; ++l) {
+    A.p[A.n] = F.W[l];
+    A.size[A.n++] = (long)T.dims[l] * T.dims[l + 1];
+    A.p[A.n] = F.bvec[l];
+    A.size[A.n++] = T.dims[l + 1];
+    if (T.ln && l + 1 < T.nl) {
+      A.p[A.n] = F.lng[l];
+      A.size[A.n++] = T.dims[l + 1];
+      A.p[A.n] = F.lnb[l];
+      A.size[A.n++] = T.dims[l + 1];
+    }
+  }
+  A.m = F.m; A.v = F.v;
+  A.lr = F.lr; A.b1 = F.b1; A.b2 = F.b2; A.eps = F.eps;
   int step = F.adam_step;
   for (int it = 0; it < F.n_iter; ++it) {
     for (int mb = 0; mb < F.n_mb; ++mb) {
       const int r0 = (int)((long)mb * F.rows / F.n_mb), r1 = (int)((long)(mb + 1) * F.rows / F.n_mb);
-      const int B = r1 - r0;
-      if (B <= 0) continue;
-      const long nx = (long)B * T.dims[0];
-      hipLaunchKernelGGL(k_gather_rows, dim3((unsigned)((nx + 255) / 256)), dim3(256), 0, s, F.obs, F.targets,
-                         F.perm + (long)it * F.rows + r0, B, T.dims[0], F.obs_mean, F.obs_inv_std, F.x, F.y);
-      T.M = B;
-      T.x0 = F.x;
-      theta_hidden(T, s);
-      theta_output(T, F.vbuf, s);
-      if (F.loss_out)
-        hipLaunchKernelGGL(k_mse_loss, dim3(1), dim3(256), 0, s, F.vbuf, F.y, B, F.loss_out + it * F.n_mb + mb);
-      hipLaunchKernelGGL(k_mse_seed, dim3((unsigned)((B + 255) / 256)), dim3(256), 0, s, F.vbuf, F.y, B, T.d0);
-      theta_backward(T, s);
-      ++step;
-      const real bc1 = RL(1.0) - (real)pow((double)F.b1, (double)step);
-      const real bc2 = RL(1.0) - (real)pow((double)F.b2, (double)step);
-      // one Adam launch over all layers (the flat gradient holds W_0, b_0, W_1, ... in order;
-      // with layer normalisation a hidden layer's gain and bias follow its W, b)
-      LearnAdamT<real> A = {};
-      A.n = 0;
-      for (int l = 0; l < T.nl; ++l) {
-        A.p[A.n] = F.W[l];
-        A.size[A.n++] = (long)T.dims[l] * T.dims[l + 1];
-        A.p[A.n] = F.bvec[l];
-        A.size[A.n++] = T.dims[l + 1];
-        if (T.ln && l + 1 < T.nl) {
-          A.p[A.n] = F.lng[l];
-          A.size[A.n++] = T.dims[l + 1];
-          A.p[A.n] = F.lnb[l];
-          A.size[A.n++] = T.dims[l + 1];
-        }
+      if (r1 <= r0) continue;
+      T.M = r1 - r0;
+      const int* perm = F.perm + (long)it * F.rows + r0;
+      FitArgs g = {};
+      int rt;
+      size_t lds;
+      if (fit_plan(F, T.M, g, rt, lds)) {
+        g.N = mlp_net(T);
+        g.perm = perm;
+        g.tgt = F.targets;
+        g.part = F.scratch;
+        g.loss_part = F.y;
+        g.np = (int)mlp_params(T);
+        g.ow1 = (int)T.off_w[1]; g.ow2 = (int)T.off_w[2];
+        g.ob0 = (int)T.off_b[0]; g.ob1 = (int)T.off_b[1]; g.ob2 = (int)T.off_b[2];
+        g.og1 = (int)T.off_g[0]; g.og2 = (int)T.off_g[1];
+        const int tiles = (T.M + 16 * rt - 1) / (16 * rt);
+        const int bad = T.ln ? (rt == 2 ? launch_fit_as<2, true>(g, tiles, lds, s) : launch_fit_as<1, true>(g, tiles, lds, s))
+                             : (rt == 2 ? launch_fit_as<2, false>(g, tiles, lds, s) : launch_fit_as<1, false>(g, tiles, lds, s));
+        if (bad) return -1;
+        reduce_args(Q, T, F.scratch, tiles, 0, false);
+        Q.n_loss = tiles;
+      } else {
+        RowsArgs R = {};
+        R.perm = perm;
+        R.tgt = F.targets;
+        R.xs = F.x;
+        R.V = F.vbuf;
+        R.loss_part = F.y;
+        int blocks = 0;
+        if (launch_rows<ROWS_FIT>(R, T, &blocks, &Q.n_loss, s)) return -1;
+        WgradArgs W = {};
+        W.N = R.N;
+        W.dv = F.vbuf;
+        W.xs = F.x;
+        launch_wgrad(W, T, s);
+        reduce_args(Q, T, W.part, W.splits, blocks, true);
       }
-      A.g = T.out; A.m = F.m; A.v = F.v;
-      A.lr = F.lr; A.b1 = F.b1; A.b2 = F.b2; A.eps = F.eps; A.bc1 = bc1; A.bc2 = bc2;
-      launch_adam_multi(A, s);
+      Q.rows = T.M;
+      Q.loss_out = F.loss_out ? F.loss_out + it * F.n_mb + mb : nullptr;
+      ++step;
+      A.bc1 = RL(1.0) - (real)pow((double)F.b1, (double)step);
+      A.bc2 = RL(1.0) - (real)pow((double)F.b2, (double)step);
+      Q.A = A;
+      hipLaunchKernelGGL(k_mlp_reduce, dim3((unsigned)((Q.np + SIM_WAVE - 1) / SIM_WAVE) + 1), dim3(RD_WAVES * SIM_WAVE), 0, s, Q);
     }
   }
   return hipGetLastError() == hipSuccess ? 0 : -1;

@@ -145,8 +145,8 @@ struct MlpArgsT {
   const T* lnb[SIM_MAXL];      // [out] bias of hidden layer l (caller)
 };
 
-// blocks of the policy-gradient pass's layer-normalisation adjoint (fixed: their partial sums
-// are reduced in block order, so the result does not depend on the row count)
+// the gain / bias partial sums of a layer-normalised network's rows pass are sized for this many
+// blocks of the widest layer
 #define SIM_LN_BLOCKS 256
 
 // phases of the window kernels' profile (a build with -DSIM_PHASE_PROFILE; ids in sim_math.h)
@@ -228,7 +228,6 @@ struct ThetaArgsT {
   int M;                      // rows: h * N
   int nl;                     // linear layers of the actor
   int dims[SIM_MAXL + 1];
-  int splits;                 // row chunks of the weight-gradient reductions
   const T* W[SIM_MAXL];       // [out][in] caller weights
   const T* b[SIM_MAXL];
   const T* x0;                // [M][dims[0]] observations o_0 .. o_{h-1}
@@ -243,15 +242,16 @@ struct ThetaArgsT {
   T* H[SIM_MAXL];             // H[l] (l >= 1): [M][dims[l]] hidden activations
   long ldH[SIM_MAXL];         // row stride of H[l] (0: dims[l])
   int hidden_given;           // H holds the activations already (the window's own): no recompute
-  T* d0;                      // [M][max dim] layer adjoints (ping-pong)
-  T* d1;
-  T* part;                    // [splits][max out*(in+1)] partial weight gradients
+  T* d0;                      // [M][dims[1]] adjoint of the first hidden layer's pre-activations
+  T* d1;                      // [M][dims[2]] of the second's
+  T* part;                    // partial weight gradients, part_cap values
+  long part_cap;
   T* out;                     // flat dL/dtheta: W_0, b_0, W_1, b_1, ...
   long off_w[SIM_MAXL], off_b[SIM_MAXL];
   // layer normalisation of the hidden layers: H[l] then holds the ELU outputs, st + r * ldst
   // the per-row mean and inverse deviation of each hidden layer (the window's, or computed by
   // the hidden-layer pass with ln_eps), Y[l] ([M][dims[l]], scratch) the normalised layer
-  // inputs, lnpart ([ln_blocks][2][max width]) the per-block partial sums of the gain and bias
+  // inputs, lnpart (lnpart_cap values) the per-block partial sums of the gain and bias
   // gradients (flat at off_g / off_beta)
   int ln;
   T ln_eps;
@@ -261,7 +261,7 @@ struct ThetaArgsT {
   long ldst;
   T* Y[SIM_MAXL];
   T* lnpart;
-  int ln_blocks;
+  long lnpart_cap;
   long off_g[SIM_MAXL], off_beta[SIM_MAXL];
 };
 
@@ -317,8 +317,10 @@ struct CriticFitT {
   const int* perm;      // [n_iter][rows]
   int rows, n_iter, n_mb;
   T* x;                 // [rows][obs_dim] gathered minibatch
-  T* y;                 // [rows]
-  T* vbuf;              // [rows] critic outputs
+  T* y;                 // [rows] squared-error sums of the row tiles
+  T* vbuf;              // [rows] output adjoints
+  T* scratch;           // the workspace from vbuf on, scratch_cap values: the row tiles' gradients
+  long scratch_cap;
   T* W[SIM_MAXL];       // critic weights, updated in place
   T* bvec[SIM_MAXL];
   T* lng[SIM_MAXL];     // with layer normalisation: the hidden layers' gains and biases, updated

@@ -3,6 +3,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <math.h>
+#include <type_traits>
 #include "sim_types.h"
 
 // DOF counts compiled as kernels of their own: torque models (CartPole, Ant, Humanoid), muscle
