@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -199,6 +200,72 @@ static void pack_mtu_tables(DevModelT<T>& d) {
     T* pr = &d.mtu_par[i * 4];
     pr[0] = d.mtu_fmax[i]; pr[1] = d.mtu_lopt[i]; pr[2] = d.mtu_lslack[i]; pr[3] = (T)d.mtu_npt[i];
   }
+}
+
+// The muscles' summation schedule; false if the model is beyond its capacity (the kernels then
+// add with atomics, in the same order).
+static bool build_mus_sched(const DevModelT<double>& m, MusSched& S) {
+  struct Run { int flush, lane, run, body, slot; };
+  std::memset(&S, 0, sizeof(S));
+  std::vector<Run> runs[SIM_MUS_PASSES];
+  for (int p = 0; p * SIM_WAVE < m.n_mtu; ++p) {
+    for (int ln = 0; ln < SIM_WAVE && p * SIM_WAVE + ln < m.n_mtu; ++ln) {
+      const int i = p * SIM_WAVE + ln, np = m.mtu_npt[i];
+      int run = 0;
+      for (int k = 1; k <= np; ++k) {
+        const int body = m.mtu_body[(k - 1) * SIM_MAXMTU + i];
+        // a run ends before the first point on another body, or after the last point
+        if (k == np || m.mtu_body[k * SIM_MAXMTU + i] != body)
+          runs[p].push_back(Run{k == np ? SIM_MAXMPT : k, ln, run++, body, 0});
+      }
+      if (run > SIM_MUS_RUNS) return false;
+    }
+    if (runs[p].size() > SIM_MUS_SLOTS) return false;
+    std::sort(runs[p].begin(), runs[p].end(),
+              [](const Run& a, const Run& b) { return a.flush != b.flush ? a.flush < b.flush : a.lane < b.lane; });
+    for (size_t s = 0; s < runs[p].size(); ++s) {
+      runs[p][s].slot = (int)s;
+      S.slot[p * SIM_WAVE + runs[p][s].lane][runs[p][s].run] = (unsigned short)s;
+    }
+  }
+  auto build = [&](int copies, int rounds, int chunks, int* nch, unsigned short* list, unsigned short* fold, int fw) {
+    int pair_of[16][SIM_MAXJ], n = 0;
+    for (auto& row : pair_of)
+      for (int& x : row) x = -1;
+    for (int p = 0; p < SIM_MUS_PASSES; ++p)
+      for (const Run& r : runs[p]) {
+        int& q = pair_of[r.lane % copies][r.body];
+        if (q < 0) q = n++;
+      }
+    if (n > rounds * SIM_MUS_QL) return false;
+    const size_t per_chunk = (size_t)rounds * SIM_WAVE * SIM_MUS_CHUNK;
+    for (int p = 0; p < SIM_MUS_PASSES; ++p) {
+      std::vector<std::vector<int>> of(n);
+      size_t longest = 0;
+      for (const Run& r : runs[p]) of[pair_of[r.lane % copies][r.body]].push_back(r.slot);
+      for (const auto& v : of) longest = std::max(longest, v.size());
+      nch[p] = (int)((longest + SIM_MUS_CHUNK - 1) / SIM_MUS_CHUNK);
+      if (nch[p] > chunks) return false;
+      for (int c = 0; c < chunks; ++c)
+        for (int r = 0; r < rounds; ++r)
+          for (int ln = 0; ln < SIM_WAVE; ++ln)
+            for (int u = 0; u < SIM_MUS_CHUNK; ++u) {
+              const int q = r * SIM_MUS_QL + ln / 6, e = c * SIM_MUS_CHUNK + u;
+              const bool in = ln < 6 * SIM_MUS_QL && q < n && e < (int)of[q].size();
+              list[(p * (size_t)chunks + c) * per_chunk + ((size_t)r * SIM_WAVE + ln) * SIM_MUS_CHUNK + u] =
+                  (unsigned short)((ln % 6) * (SIM_MUS_SLOTS + 1) + (in ? of[q][e] : SIM_MUS_SLOTS));
+            }
+    }
+    for (int e = 0; e < 3 * SIM_WAVE; ++e)
+      for (int c = 0; c < fw; ++c) {
+        const int q = c < copies ? pair_of[c][e / 6] : -1;
+        fold[e * fw + c] = (unsigned short)(q >= 0 ? q * 6 + e % 6 : rounds * SIM_MUS_QL * 6);
+      }
+    return true;
+  };
+  static_assert(3 * SIM_WAVE == SIM_MAXJ * 6, "three rounds of entries");
+  return build(SIM_MUS_CF, SIM_MUS_RF, SIM_MUS_KF, S.nch_f, &S.lf[0][0][0][0][0], &S.ff[0][0][0], 12) &&
+         build(SIM_MUS_CA, SIM_MUS_RA, SIM_MUS_KA, S.nch_a, &S.la[0][0][0][0][0], &S.fa[0][0][0], 4);
 }
 
 template <typename T>
@@ -598,7 +665,27 @@ extern "C" int sim_create(const SimModelDesc* md, const SimOptions* opt, SimHand
   }
   size_t msz = (opt->precision == SIM_PREC_FP64) ? sizeof(DevModelT<double>) : sizeof(DevModelT<float>);
   const void* src = (opt->precision == SIM_PREC_FP64) ? (const void*)&h->m64 : (const void*)&h->m32;
-  if (hipMalloc(&h->dev_model, msz) != hipSuccess) { delete h; return fail(SIM_E_HIP, "hipMalloc failed"); }
+  // a muscle model's summation schedule follows the model
+  std::unique_ptr<MusSched> mus;
+  if (m.n_mtu > 0) {
+    mus.reset(new MusSched);
+    if (build_mus_sched(m, *mus)) {
+      h->m32.mus_off = h->m64.mus_off = (int)align256(msz);
+      int nch = 0;
+      for (int p = 0; p < SIM_MUS_PASSES; ++p) nch |= mus->nch_f[p] << (4 * p) | mus->nch_a[p] << (12 + 4 * p);
+      h->m32.mus_nch = h->m64.mus_nch = nch;
+    } else {
+      mus.reset();
+    }
+  }
+  if (hipMalloc(&h->dev_model, mus ? align256(msz) + sizeof(MusSched) : msz) != hipSuccess) {
+    delete h;
+    return fail(SIM_E_HIP, "hipMalloc failed");
+  }
+  if (mus && hipMemcpy(static_cast<char*>(h->dev_model) + align256(msz), mus.get(), sizeof(MusSched),
+                       hipMemcpyHostToDevice) != hipSuccess) {
+    hipFree(h->dev_model); delete h; return fail(SIM_E_HIP, "hipMemcpy failed");
+  }
   if (hipMemcpy(h->dev_model, src, msz, hipMemcpyHostToDevice) != hipSuccess) {
     hipFree(h->dev_model); delete h; return fail(SIM_E_HIP, "hipMemcpy failed");
   }

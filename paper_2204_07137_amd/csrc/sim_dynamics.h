@@ -32,11 +32,14 @@ struct ContactRegs {
 
 // Muscle accumulators: a table of SIM_MAXJ x 6 values padded to an odd stride (so the copies
 // of one entry sit in different banks); the forward keeps SIM_MUS_CF copies of the wrench
-// table, the adjoint SIM_MUS_CA copies of each of its three tables.
+// table, the adjoint SIM_MUS_CA copies of each of its three tables.  The same space holds the
+// slots of the scheduled sums: two tables' slots side by side in the adjoint (the third's are in
+// the substep scratch).
 #define SIM_MUS_STRIDE (SIM_MAXJ * 6 + 1)
-#define SIM_MUS_CF 11
-#define SIM_MUS_CA 3
 static_assert(3 * SIM_MUS_CA <= SIM_MUS_CF, "adjoint muscle tables fit the forward's space");
+#define SIM_MUS_SPACE (SIM_MUS_CF * SIM_MUS_STRIDE)
+static_assert(SIM_MUS_SPACE >= 2 * 6 * (SIM_MUS_SLOTS + 1) && SIM_MUS_SPACE >= 3 * (SIM_MUS_RA * 6 * SIM_MUS_QL + 6),
+              "the slots and the pairs' sums fit the copies' space");
 
 // Per-environment LDS of one environment.  MAXA: action capacity; NMTU: muscle capacity
 // (0 for torque-driven models, whose layout then carries no muscle fields); LANES: the lanes
@@ -79,7 +82,7 @@ struct EnvLDST {
       real F[CJ][6], Fi[CJ][6];
       real Ic[CJ][10];
     };
-    real acc[CJ][42];
+    real acc[CJ][42];   // (and the third table's muscle slots)
   };
   real vec[CV];
   real O[4];
@@ -105,7 +108,7 @@ struct EnvLDST {
     double M64[CV][CV];   // FP64 refactorisation (never live at the same time as the MLP)
     // per-body muscle wrenches and their adjoint terms (substep-local), accumulated in
     // several copies (see muscle_wrenches); copy 0 of each table holds the sums
-    real mus[NMTU > 0 ? SIM_MUS_CF * SIM_MUS_STRIDE : 1];
+    real mus[NMTU > 0 ? SIM_MUS_SPACE : 1];
   };
   real red[4];
   real lnst[2 * SIM_MAXL];   // per hidden layer: mean and inverse deviation of its normalisation
@@ -488,10 +491,18 @@ __device__ __forceinline__ void lds_add6(real* dst, sv w) {
 }
 
 // Per-body wrench of all muscle tensions (about O), left in copy 0 of the wrench table
-// (mus_fm).  One lane per unit.  Many units share a body, and LDS atomics to one address
-// are serialised, so lane l adds into copy l % SIM_MUS_CF and the copies are summed
-// afterwards in copy order; an instruction's additions to one address are performed in
-// lane order, so the sums are reproducible.
+// (mus_fm).  One lane per unit.  Many units share a body: lane l belongs to copy
+// l % SIM_MUS_CF, and the copies are summed afterwards in copy order.
+//
+// The sums follow the model's schedule (MusSched): the lanes leave their runs' wrenches in slots,
+// and a lane per (copy, body, component) adds its slots in order, all in flight together; what is
+// left is bound by the instructions of one wavefront.  The additions as LDS atomics, in the same
+// order (an instruction's additions to one address are performed in lane order, so both forms
+// give the same sums bit for bit), were bound by the LDS, which performs about 1.5 of the 64
+// lanes' additions per cycle: with four 152-muscle environments on a CU they took 19 k cycles of
+// the forward substep's 75 k and 68 k of its adjoint's 206 k; the schedule takes 13 k and 23 k.
+// Models beyond the schedule's capacity (more runs per unit or pass, or pairs, than it has room
+// for) keep the atomics.
 template <class L>
 __device__ __forceinline__ real* mus_fm(L& E, int b) { return &E.mus[b * 6]; }
 template <class L>
@@ -510,18 +521,58 @@ __device__ __forceinline__ void mus_fold(L& E, int t, int nc, int ln) {
   }
 }
 
+// one slot of a table of slots: component-major, so that the lanes of a store (consecutive slots)
+// and of a component's reads fall into different banks
+#define SIM_MUS_TAB (6 * (SIM_MUS_SLOTS + 1))
+__device__ __forceinline__ void mus_put(real* slot, sv w) {
+  constexpr int S = SIM_MUS_SLOTS + 1;
+  slot[0] = w.a.x; slot[S] = w.a.y; slot[2 * S] = w.a.z;
+  slot[3 * S] = w.l.x; slot[4 * S] = w.l.y; slot[5 * S] = w.l.z;
+}
+typedef unsigned short mus_u16x4 __attribute__((ext_vector_type(4)));
+// slot of a unit's run-th run (SIM_MUS_RUNS of them at most)
+__device__ __forceinline__ int run_slot(mus_u16x4 s, int run) {
+  return run == 0 ? s[0] : (run == 1 ? s[1] : (run == 2 ? s[2] : s[3]));
+}
+
 template <class L>
 __device__ __forceinline__ void muscle_wrenches(const Scal* __restrict__ m, L& E, int ln) {
-  for (int i = ln; i < SIM_MUS_CF * SIM_MUS_STRIDE; i += SIM_WAVE) E.mus[i] = RL(0.0);
+  const MusSched* __restrict__ MS = m->mus;
+  const bool sched = MS != nullptr;
+  if (sched) {
+    if (ln < 6) E.mus[ln * (SIM_MUS_SLOTS + 1) + SIM_MUS_SLOTS] = RL(0.0);
+  } else {
+    for (int i = ln; i < SIM_MUS_CF * SIM_MUS_STRIDE; i += SIM_WAVE) E.mus[i] = RL(0.0);
+  }
   wsync();
   real* fm = &E.mus[(ln % SIM_MUS_CF) * SIM_MUS_STRIDE];
+  real sum[SIM_MUS_RF];
+#pragma unroll
+  for (int r = 0; r < SIM_MUS_RF; ++r) sum[r] = RL(0.0);
   SIM_PHASE(E, PH_F_MUSCLE);
   for (int i0 = 0; i0 < m->n_mtu; i0 += SIM_WAVE) {
-    const int i = i0 + ln;
+    const int i = i0 + ln, p = i0 / SIM_WAVE;
+    // the pass's schedule is requested before its paths are formed
+    mus_u16x4 slots = {}, o[SIM_MUS_RF] = {};
+    if (sched) {
+      slots = *reinterpret_cast<const mus_u16x4*>(&MS->slot[i < m->n_mtu ? i : 0][0]);
+#pragma unroll
+      for (int r = 0; r < SIM_MUS_RF; ++r) o[r] = *reinterpret_cast<const mus_u16x4*>(&MS->lf[p][0][r][ln][0]);
+      __asm__ volatile("" ::: "memory");
+    }
     if (i < m->n_mtu) {
       MtuPath P;
       mtu_path(m, E, i, P, E.act[i]);
       SIM_PHASE(E, PH_FM_PATH);
+      int run = 0;
+      auto leave = [&](int body, sv w) __attribute__((always_inline)) {
+        if (sched) {
+          mus_put(&E.mus[run_slot(slots, run)], w);
+          ++run;
+        } else {
+          lds_add6(fm + body * 6, w);
+        }
+      };
       // consecutive points on one body are summed first: one addition per run of points
       sv acc = zsv();
       int cur = P.b[0];
@@ -530,7 +581,7 @@ __device__ __forceinline__ void muscle_wrenches(const Scal* __restrict__ m, L& E
         if (k < P.np) {
           const sv w = spf(P.x[k], scl3(mtu_udiff(P, k), P.F));
           if (P.b[k] != cur) {
-            lds_add6(fm + cur * 6, acc);
+            leave(cur, acc);
             acc = w;
             cur = P.b[k];
           } else {
@@ -538,12 +589,60 @@ __device__ __forceinline__ void muscle_wrenches(const Scal* __restrict__ m, L& E
           }
         }
       }
-      lds_add6(fm + cur * 6, acc);
-      SIM_PHASE(E, PH_FM_ACC);
+      leave(cur, acc);
     }
+    if (sched) {
+      wsync();
+      const int nch = (m->mus_nch >> (4 * p)) & 15;
+      for (int c = 0; c < nch; ++c) {
+        if (c > 0) {
+#pragma unroll
+          for (int r = 0; r < SIM_MUS_RF; ++r) o[r] = *reinterpret_cast<const mus_u16x4*>(&MS->lf[p][c][r][ln][0]);
+          __asm__ volatile("" ::: "memory");
+        }
+#pragma unroll
+        for (int r0 = 0; r0 < SIM_MUS_RF; r0 += 6) {
+          real v[6][SIM_MUS_CHUNK];
+#pragma unroll
+          for (int r = 0; r < 6; ++r)
+#pragma unroll
+            for (int u = 0; u < SIM_MUS_CHUNK; ++u) v[r][u] = E.mus[o[r0 + r][u]];
+          __asm__ volatile("" ::: "memory");
+#pragma unroll
+          for (int r = 0; r < 6; ++r)
+#pragma unroll
+            for (int u = 0; u < SIM_MUS_CHUNK; ++u) sum[r0 + r] += v[r][u];
+        }
+      }
+      wsync();
+    }
+    SIM_PHASE(E, PH_FM_ACC);
   }
-  wsync();
-  mus_fold(E, 0, SIM_MUS_CF, ln);
+  if (sched) {
+    // the pairs' sums, then the copies of each entry in copy order
+    if (ln < 6 * SIM_MUS_QL) {
+#pragma unroll
+      for (int r = 0; r < SIM_MUS_RF; ++r) E.mus[r * 6 * SIM_MUS_QL + ln] = sum[r];
+    } else if (ln == 6 * SIM_MUS_QL) {
+      E.mus[SIM_MUS_RF * 6 * SIM_MUS_QL] = RL(0.0);
+    }
+    wsync();
+    real s[3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      const mus_u16x4* f = reinterpret_cast<const mus_u16x4*>(&MS->ff[r][ln][0]);
+      const mus_u16x4 f0 = f[0], f1 = f[1], f2 = f[2];
+      s[r] = E.mus[f0[0]];
+#pragma unroll
+      for (int c = 1; c < SIM_MUS_CF; ++c) s[r] += E.mus[c < 4 ? f0[c & 3] : (c < 8 ? f1[c & 3] : f2[c & 3])];
+    }
+    wsync();
+#pragma unroll
+    for (int r = 0; r < 3; ++r) E.mus[r * SIM_WAVE + ln] = s[r];
+  } else {
+    wsync();
+    mus_fold(E, 0, SIM_MUS_CF, ln);
+  }
   wsync();
 }
 
@@ -555,8 +654,22 @@ __device__ __forceinline__ void muscle_wrenches(const Scal* __restrict__ m, L& E
 // the tension and the segment directions.
 template <class L>
 __device__ __forceinline__ void muscle_adjoint(const Scal* __restrict__ m, L& E, int ln) {
-  for (int i = ln; i < 3 * SIM_MUS_CA * SIM_MUS_STRIDE; i += SIM_WAVE) E.mus[i] = RL(0.0);
+  const MusSched* __restrict__ MS = m->mus;
+  const bool sched = MS != nullptr;
+  // slots (see muscle_wrenches): the wrenches' and the position terms' side by side, the
+  // velocity terms' in the substep scratch, which is free until the per-body terms
+  real* const slot_v = &E.acc[0][0];
+  static_assert(sizeof(E.acc) >= SIM_MUS_TAB * sizeof(real), "slots of the third table");
+  if (sched) {
+    if (ln < 12) E.mus[ln * (SIM_MUS_SLOTS + 1) + SIM_MUS_SLOTS] = RL(0.0);
+    if (ln < 6) slot_v[ln * (SIM_MUS_SLOTS + 1) + SIM_MUS_SLOTS] = RL(0.0);
+  } else {
+    for (int i = ln; i < 3 * SIM_MUS_CA * SIM_MUS_STRIDE; i += SIM_WAVE) E.mus[i] = RL(0.0);
+  }
   wsync();
+  real sf[SIM_MUS_RA], sa[SIM_MUS_RA], sw[SIM_MUS_RA];
+#pragma unroll
+  for (int r = 0; r < SIM_MUS_RA; ++r) sf[r] = sa[r] = sw[r] = RL(0.0);
   // lane l adds into copy l % SIM_MUS_CA of each table (see muscle_wrenches)
   const int cp = ln % SIM_MUS_CA;
   real* fm = &E.mus[cp * SIM_MUS_STRIDE];
@@ -564,7 +677,17 @@ __device__ __forceinline__ void muscle_adjoint(const Scal* __restrict__ m, L& E,
   real* mvb = &E.mus[(2 * SIM_MUS_CA + cp) * SIM_MUS_STRIDE];
   SIM_PHASE(E, PH_A_MUSCLE);
   for (int i0 = 0; i0 < m->n_mtu; i0 += SIM_WAVE) {
-    const int i = i0 + ln;
+    const int i = i0 + ln, p = i0 / SIM_WAVE;
+    constexpr int PRE = 3;   // chunks of the schedule requested before the paths are formed
+    mus_u16x4 slots = {}, o[PRE][SIM_MUS_RA] = {};
+    if (sched) {
+      slots = *reinterpret_cast<const mus_u16x4*>(&MS->slot[i < m->n_mtu ? i : 0][0]);
+#pragma unroll
+      for (int c = 0; c < PRE; ++c)
+#pragma unroll
+        for (int r = 0; r < SIM_MUS_RA; ++r) o[c][r] = *reinterpret_cast<const mus_u16x4*>(&MS->la[p][c][r][ln][0]);
+      __asm__ volatile("" ::: "memory");
+    }
     if (i < m->n_mtu) {
       const real act = E.act[i];
       MtuPath P;
@@ -602,6 +725,20 @@ __device__ __forceinline__ void muscle_adjoint(const Scal* __restrict__ m, L& E,
         }
       }
       SIM_PHASE(E, PH_AM_DERIV);
+      int run = 0;
+      auto leave = [&](int body, sv f, sv a, sv v) __attribute__((always_inline)) {
+        if (sched) {
+          const int slot = run_slot(slots, run);
+          mus_put(&E.mus[slot], f);
+          mus_put(&E.mus[SIM_MUS_TAB + slot], a);
+          mus_put(&slot_v[slot], v);
+          ++run;
+        } else {
+          lds_add6(fm + body * 6, f);
+          lds_add6(mab + body * 6, a);
+          lds_add6(mvb + body * 6, v);
+        }
+      };
       // consecutive points on one body are summed first (see muscle_wrenches)
       sv af = zsv(), aa = zsv(), av = zsv();
       int cur = P.b[0];
@@ -617,9 +754,7 @@ __device__ __forceinline__ void muscle_adjoint(const Scal* __restrict__ m, L& E,
                                    mk3(RL(0.0), RL(0.0), RL(0.0))));
           const sv wv = spf(P.x[k], vb);
           if (P.b[k] != cur) {
-            lds_add6(fm + cur * 6, af);
-            lds_add6(mab + cur * 6, aa);
-            lds_add6(mvb + cur * 6, av);
+            leave(cur, af, aa, av);
             af = wf; aa = wa; av = wv;
             cur = P.b[k];
           } else {
@@ -627,14 +762,83 @@ __device__ __forceinline__ void muscle_adjoint(const Scal* __restrict__ m, L& E,
           }
         }
       }
-      lds_add6(fm + cur * 6, af);
-      lds_add6(mab + cur * 6, aa);
-      lds_add6(mvb + cur * 6, av);
-      SIM_PHASE(E, PH_AM_ACC);
+      leave(cur, af, aa, av);
     }
+    if (sched) {
+      wsync();
+      const int nch = (m->mus_nch >> (12 + 4 * p)) & 15;
+      auto add = [&](const mus_u16x4 (&q)[SIM_MUS_RA]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r0 = 0; r0 < SIM_MUS_RA; r0 += 2) {
+          real v[2][SIM_MUS_CHUNK][3];
+#pragma unroll
+          for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int u = 0; u < SIM_MUS_CHUNK; ++u) {
+              const int w = q[r0 + r][u];
+              v[r][u][0] = E.mus[w];
+              v[r][u][1] = E.mus[SIM_MUS_TAB + w];
+              v[r][u][2] = slot_v[w];
+            }
+          __asm__ volatile("" ::: "memory");
+#pragma unroll
+          for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int u = 0; u < SIM_MUS_CHUNK; ++u) {
+              sf[r0 + r] += v[r][u][0];
+              sa[r0 + r] += v[r][u][1];
+              sw[r0 + r] += v[r][u][2];
+            }
+        }
+      };
+#pragma unroll
+      for (int c = 0; c < PRE; ++c)
+        if (c < nch) add(o[c]);
+      for (int c = PRE; c < nch; ++c) {
+        mus_u16x4 q[SIM_MUS_RA];
+#pragma unroll
+        for (int r = 0; r < SIM_MUS_RA; ++r) q[r] = *reinterpret_cast<const mus_u16x4*>(&MS->la[p][c][r][ln][0]);
+        __asm__ volatile("" ::: "memory");
+        add(q);
+      }
+      wsync();
+    }
+    SIM_PHASE(E, PH_AM_ACC);
   }
-  wsync();
-  for (int t = 0; t < 3; ++t) mus_fold(E, t, SIM_MUS_CA, ln);
+  if (sched) {
+    constexpr int NT = SIM_MUS_RA * 6 * SIM_MUS_QL, ST = NT + 6;   // a table's pairs, and a zero
+    if (ln <= 6 * SIM_MUS_QL) {
+      const bool on = ln < 6 * SIM_MUS_QL;
+#pragma unroll
+      for (int r = 0; r < SIM_MUS_RA; ++r)
+        if (on || r == SIM_MUS_RA - 1) {
+          const int w = r * 6 * SIM_MUS_QL + ln;   // lane 60 of the last round: the zero
+          E.mus[w] = on ? sf[r] : RL(0.0);
+          E.mus[ST + w] = on ? sa[r] : RL(0.0);
+          E.mus[2 * ST + w] = on ? sw[r] : RL(0.0);
+        }
+    }
+    wsync();
+    real s[3][3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      const mus_u16x4 f = *reinterpret_cast<const mus_u16x4*>(&MS->fa[r][ln][0]);
+#pragma unroll
+      for (int t = 0; t < 3; ++t) {
+        s[t][r] = E.mus[t * ST + f[0]];
+#pragma unroll
+        for (int c = 1; c < SIM_MUS_CA; ++c) s[t][r] += E.mus[t * ST + f[c]];
+      }
+    }
+    wsync();
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+      for (int r = 0; r < 3; ++r) E.mus[t * SIM_MUS_CA * SIM_MUS_STRIDE + r * SIM_WAVE + ln] = s[t][r];
+  } else {
+    wsync();
+    for (int t = 0; t < 3; ++t) mus_fold(E, t, SIM_MUS_CA, ln);
+  }
   wsync();
 }
 

@@ -19,9 +19,11 @@ struct Scal {
   int n_mtu, n_motor, nck;
   int tape_nw;           // 16-byte chunks of a packed tape entry
   int fc_nw;             // 16-byte chunks of a factor-cache entry
+  int mus_nch;           // chunks of the muscles' schedule per pass, 4 bits each: forward, then adjoint
   real dt_sub, g, kn, kd, kt, mu, klim, chol_thr;
   real tau_act, fl_w, vmax, term_h;
   const DevModel* tab;   // the model's tables (muscle paths) in global memory
+  const MusSched* mus;   // the muscles' summation schedule, or null
 };
 __device__ __forceinline__ Scal load_scal(const DevModel* __restrict__ m) {
   Scal s;
@@ -36,6 +38,7 @@ __device__ __forceinline__ Scal load_scal(const DevModel* __restrict__ m) {
   s.tape_nw = m->tape_nw;
   s.fc_nw = m->fc_nw;
   s.tab = m;
+  s.mus = m->mus_off ? reinterpret_cast<const MusSched*>(reinterpret_cast<const char*>(m) + m->mus_off) : nullptr;
   return s;
 }
 

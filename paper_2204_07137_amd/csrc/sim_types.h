@@ -81,9 +81,40 @@ static inline size_t sim_bf16_tiles_bytes(int n_rows, int n_k) {
 enum { J_FREE = 0, J_HINGE = 1, J_SLIDE = 2 };
 enum { TASK_NONE = 0, TASK_CARTPOLE = 1, TASK_ANT = 2, TASK_HUMANOID = 3, TASK_MTU = 4 };
 
+// How the muscles' point forces are summed per body without atomics (sim_dynamics.h): a unit's
+// consecutive points on one body form a run; a run leaves its six-component wrench in a slot of
+// its pass of 64 units, and every (copy, body) pair of accumulators adds its slots in the order
+// in which the runs end: by pass, by the point after the run, by lane.  Six lanes (one per
+// component) serve a pair, ten pairs a round of the wavefront, SIM_MUS_CHUNK slots at a time.  A
+// table of slots is component-major, component c of slot s at c (SIM_MUS_SLOTS + 1) + s, and slot
+// references include the component; a pass numbers its slots in the order in which they are
+// stored, so that a store's lanes fall into different banks; the last slot holds zeros.
+#define SIM_MUS_PASSES ((SIM_MAXMTU + SIM_WAVE - 1) / SIM_WAVE)
+#define SIM_MUS_CF 11        // copies of the forward's wrench table
+#define SIM_MUS_CA 3         // copies of each of the adjoint's three tables
+#define SIM_MUS_RF 12        // rounds of pairs, forward
+#define SIM_MUS_RA 4         // and adjoint
+#define SIM_MUS_QL 10        // pairs per round
+#define SIM_MUS_CHUNK 4
+#define SIM_MUS_KF 2         // most chunks of a pass, forward
+#define SIM_MUS_KA 6         // and adjoint
+#define SIM_MUS_SLOTS 160    // slots of a pass (slot SIM_MUS_SLOTS: zeros)
+#define SIM_MUS_RUNS 4       // most runs of a unit
+struct MusSched {
+  int nch_f[SIM_MUS_PASSES], nch_a[SIM_MUS_PASSES];   // chunks per pass (kernels: mus_nch)
+  unsigned short slot[SIM_MAXMTU][SIM_MUS_RUNS] __attribute__((aligned(16)));   // the unit's runs' slots
+  unsigned short lf[SIM_MUS_PASSES][SIM_MUS_KF][SIM_MUS_RF][SIM_WAVE][SIM_MUS_CHUNK] __attribute__((aligned(16)));
+  unsigned short la[SIM_MUS_PASSES][SIM_MUS_KA][SIM_MUS_RA][SIM_WAVE][SIM_MUS_CHUNK] __attribute__((aligned(16)));
+  // where entry (body, component) = 64 r + lane finds each copy's sum (pair, component), or a zero
+  unsigned short ff[3][SIM_WAVE][12] __attribute__((aligned(16)));
+  unsigned short fa[3][SIM_WAVE][4] __attribute__((aligned(16)));
+};
+
 template <typename T>
 struct DevModelT {
   int J, nq, nv, na, nc, ns, od, task, floating, has_last_action, substeps, max_depth;
+  int mus_off;               // bytes from the model to its MusSched on the device (0: none)
+  int mus_nch;               // its chunks per pass, 4 bits each: forward passes, then adjoint passes
   int n_mtu, n_motor, nck;   // muscles; motors (the first n_motor actions); nq + nv + n_mtu
   int term;                  // early termination below term_h (root height)
   T dt_sub, g, kn, kd, kt, mu, klim;

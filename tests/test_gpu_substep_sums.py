@@ -1,0 +1,70 @@
+"""GPU parity, against the FP64 oracle through the C ABI, of the sums a substep is made of, at the
+sizes where they take another route.
+
+* The muscles' wrenches per body: along the host-made schedule up to its capacities (runs of a
+  unit, slots of a pass, slots a pair of accumulators adds per pass), by atomics beyond them.
+"""
+import numpy as np
+import pytest
+import torch
+
+import paper_2204_07137_amd as P
+import workloads as wl
+from oracle import oracle_window_grads
+from workloads.models import MTU_MAX_POINTS
+
+pytestmark = pytest.mark.gpu
+
+
+def relnorm(x, y):
+    x, y = np.asarray(x, np.float64), np.asarray(y, np.float64)
+    return float(np.linalg.norm(x - y) / max(np.linalg.norm(y), 1e-300))
+
+
+def _np(d):
+    return {k: v.double().cpu().numpy() for k, v in d.items() if torch.is_tensor(v)}
+
+
+def _arms(n, runs):
+    """The muscle arm with n units whose points alternate between cart and pole `runs` times; the
+    last run has a second point where the unit has room for it."""
+    md = wl.muscle_arm()
+    rng = np.random.default_rng([n, runs])
+    bodies, pos, npt = [], [], []
+    for _ in range(n):
+        b = [k % 2 for k in range(runs)]
+        if runs < MTU_MAX_POINTS:
+            b.append(b[-1])
+        p = [np.array([rng.uniform(0.2, 0.4), 0.0, rng.uniform(-0.1, 0.1)]) if x == 0 else
+             np.array([rng.uniform(-0.05, 0.05), 0.0, rng.uniform(0.4, 0.9)]) for x in b]
+        npt.append(len(b))
+        bodies.append(b + [0] * (MTU_MAX_POINTS - len(b)))
+        pos.append(p + [np.zeros(3)] * (MTU_MAX_POINTS - len(b)))
+    length = 0.7 * runs
+    md.update(n_mtu=n, na=n, mtu_npt=np.array(npt, np.int32), mtu_body=np.array(bodies, np.int32),
+              mtu_pos=np.array(pos, float), mtu_fmax=np.full(n, 50.0 / n), mtu_lopt=np.full(n, 0.7 * length),
+              mtu_lslack=np.full(n, 0.3 * length))
+    return md
+
+
+# 36 units of 4 runs fill the adjoint's lists exactly, 37 do not fit; 64 units of 2 runs fill a
+# pass, 65 and 160 take two and three; 64 units of 3 runs need more slots than a pass has; 5 runs
+# are more than a unit may have.
+@pytest.mark.parametrize("n,runs", [(1, 2), (36, 4), (37, 4), (64, 2), (65, 2), (160, 2), (64, 3), (8, 5)])
+def test_muscle_sums(n, runs):
+    """Tolerances: ten times those of one muscle over a full window, for sums of up to 160."""
+    print(f"[sums] {n} units of {runs} runs", flush=True)
+    md, h, N = _arms(n, runs), 2, 2
+    rng = np.random.default_rng(5)
+    s0 = np.concatenate([rng.normal(0, 0.1, (N, 1)), rng.uniform(-0.5, 0.5, (N, 1)), rng.normal(0, 0.3, (N, 2)),
+                         rng.uniform(0.0, 1.0, (N, n))], 1)
+    u = rng.uniform(0.05, 0.95, (h, N, n))
+    critic = [(rng.normal(size=(1, 4 + n)), np.zeros(1))]
+    sim = P.Sim(md, N, h, None, [4 + n, 1], ckpt_interval=2, precision="fp64")
+    fw = sim.forward(s0, None, critic, actions_in=u)
+    ad = _np(sim.adjoint(fw))
+    torch.cuda.synchronize()
+    ref = oracle_window_grads(md, s0, h, None, critic, actions=u, n_total=N)
+    assert relnorm(_np(fw)["s_h"], ref["s_h"]) < 1e-11
+    assert relnorm(ad["dL_da"], ref["dL_da"]) < 1e-9
+    assert relnorm(ad["dL_ds0"], ref["dL_ds0"]) < 1e-9
