@@ -245,12 +245,12 @@ __device__ __forceinline__ void dq_coeffs(real u, real hh, real& c, real& s, rea
 
 // --------------------------------------------------------------- dense Cholesky (row per lane)
 // The factor of one environment lives in the registers of its wavefront: lane i holds row i
-// (row[k] = L[i][k], k <= i) and column i (col[k] = L[k][i], k >= i); dinv[k] = 1 / L[k][k]
-// is held by every lane.  NV is the compile-time DOF count: rows beyond the model's nv are
-// padded with the identity, which leaves the factor and the solution of the real block
-// unchanged, so no per-step guards are needed.
+// (row[k] = L[i][k], k < i) and column i (col[k] = L[k][i], k > i), zeros elsewhere, and its own
+// reciprocal pivot dl; dinv[k] = 1 / L[k][k] is held by every lane.  NV is the compile-time DOF
+// count: rows beyond the model's nv are padded with the identity, which leaves the factor and
+// the solution of the real block unchanged, so no per-step guards are needed.
 struct Chol {
-  real row[SIM_MAXV], col[SIM_MAXV], dinv[SIM_MAXV];
+  real row[SIM_MAXV], col[SIM_MAXV], dinv[SIM_MAXV], dl;
 };
 
 // On entry C.row[k] = M[ln][k].  Right-looking factorisation; the column-k entries of the
@@ -258,14 +258,15 @@ struct Chol {
 template <int NV, int LN>
 __device__ __forceinline__ void chol_factor(Chol& C, int ln, real& minpiv) {
   minpiv = RL(3.0e38);
+  real pv = RL(1.0);
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
     real piv = bcast<LN>(C.row[k], k);
     minpiv = m_fmin(minpiv, piv);
     real inv = m_rsqrt(piv);
-    real d = piv * inv;
+    pv = (ln >= k) ? C.row[k] : pv;   // ends with the lane's own pivot
     C.dinv[k] = inv;
-    real lk = (ln == k) ? d : C.row[k] * inv;
+    real lk = (ln > k) ? C.row[k] * inv : RL(0.0);
     C.row[k] = lk;
     real ljk[NV];
 #pragma unroll
@@ -273,23 +274,39 @@ __device__ __forceinline__ void chol_factor(Chol& C, int ln, real& minpiv) {
 #pragma unroll
     for (int j = k + 1; j < NV; ++j) C.row[j] = m_fma(-lk, ljk[j], C.row[j]);
   }
+  C.dl = m_rsqrt(pv);
 }
 
-// solve L L^T x = b for b given in lane ln (row ln)
-template <int NV, int LN>
-__device__ __forceinline__ real chol_solve(const Chol& C, int ln, real b) {
+// solve L L^T x = b for b given in lane ln (row ln).  A solve is a chain of 2 NV broadcasts that
+// one wavefront issues alone, so its instructions are its time: with the rows and columns held
+// zero outside the triangle every lane takes every step (y - 0 t = y), a step being a broadcast,
+// a scaling and a product instead of these and two selects (27 DOFs: 2.6 k cycles before, 1.7 k now).
+// A lane keeps y_k unscaled and scales its own at the end of a sweep, the same product as the
+// broadcast's.  Where the solution is not finite, 0 t would not be zero: the solve is then
+// repeated with the lanes outside the triangle left alone.
+template <int NV, int LN, bool SELECT>
+__device__ __forceinline__ real chol_sweeps(const Chol& C, int ln, real b) {
   real y = b;
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
-    real yk = bcast<LN>(y, k) * C.dinv[k];
-    y = (ln == k) ? yk : (ln > k ? m_fma(-C.row[k], yk, y) : y);
+    const real yk = bcast<LN>(y, k) * C.dinv[k];
+    const real z = m_fma(-C.row[k], yk, y);
+    y = (!SELECT || ln > k) ? z : y;
   }
+  y = y * C.dl;
 #pragma unroll
   for (int k = NV - 1; k >= 0; --k) {
-    real xk = bcast<LN>(y, k) * C.dinv[k];
-    y = (ln == k) ? xk : (ln < k ? m_fma(-C.col[k], xk, y) : y);
+    const real xk = bcast<LN>(y, k) * C.dinv[k];
+    const real z = m_fma(-C.col[k], xk, y);
+    y = (!SELECT || ln < k) ? z : y;
   }
-  return y;
+  return y * C.dl;
+}
+template <int NV, int LN>
+__device__ __forceinline__ real chol_solve(const Chol& C, int ln, real b) {
+  const real x = chol_sweeps<NV, LN, false>(C, ln, b);
+  if (grp_all<LN>(ln >= NV || m_isfinite(x))) return x;
+  return chol_sweeps<NV, LN, true>(C, ln, b);
 }
 
 // --------------------------------------------------------------- FP64 fallback factorisation
@@ -1192,11 +1209,16 @@ __device__ __forceinline__ void substep_forward(const Scal* __restrict__ m, L& E
     chol64_factor<NV>(E, nv, ln);
     SIM_PHASE(E, PH_F_FACTOR);
     x = (real)chol64_solve<NV>(E, ln, (double)b);
+    // the block's upper triangle holds zeros between substeps (factor_from_block reads it)
+    if (ln < NV) {
+#pragma unroll 1
+      for (int k = ln; k < NV; ++k) E.M[ln][k] = RL(0.0);
+    }
   } else {
     wsync();
     if (ln < NV) {
 #pragma unroll
-      for (int k = 0; k < NV; ++k) E.M[ln][k] = C.row[k];   // padded rows hold the identity
+      for (int k = 0; k < NV; ++k) E.M[ln][k] = C.row[k];   // zero from the diagonal on
     }
     wsync();
     const int lc = ln < NV ? ln : 0;
@@ -1578,25 +1600,22 @@ __device__ __forceinline__ TapeMap<L> tape_map(const Scal* __restrict__ m, int l
 // the reciprocal pivots and the fallback flag into the block (both entries carry them)
 template <int NV, class L>
 __device__ __forceinline__ void stash_pivots(L& E, const Chol& C, int fb, int ln) {
-  real dv = RL(0.0);
-#pragma unroll
-  for (int k = 0; k < NV; ++k) dv = (ln == k) ? C.dinv[k] : dv;
   if (ln < L::kV) {
-    E.tdinv[ln] = dv;
+    E.tdinv[ln] = C.dl;
     E.tfb[ln] = fb ? RL(1.0) : RL(0.0);
   }
   wsync();
 }
 
-// The factor into registers from the block: the model's nv rows of the factor (lower
-// triangle) and pivots; a kernel compiled for NV > nv pads the matrix with the identity, whose
+// The factor into registers from the block: the model's nv rows of the factor (zero from the
+// diagonal on) and pivots; a kernel compiled for NV > nv pads the matrix with the identity, whose
 // factor is the identity (pivots 1), as the forward's factorisation left it.
 template <int NV, class L>
 __device__ __forceinline__ void factor_from_block(const Scal* __restrict__ m, const L& E, Chol& C, int& fb, int ln) {
   const int nv = m->nv;
   const int lr = ln < nv ? ln : 0;
   if (nv == NV) {
-    // no padding: the lanes past the matrix read row 0 and are never read by the solves
+    // no padding: the lanes past the matrix read row 0 and are never read by the solves' lanes
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
       C.row[k] = E.M[lr][k];
@@ -1606,12 +1625,12 @@ __device__ __forceinline__ void factor_from_block(const Scal* __restrict__ m, co
   } else {
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
-      const real pad = (ln == k) ? RL(1.0) : RL(0.0);
-      C.row[k] = (ln < nv && k < nv) ? E.M[lr][k] : pad;
-      C.col[k] = (ln < nv && k < nv) ? E.M[k][lr] : pad;
+      C.row[k] = (ln < nv && k < nv) ? E.M[lr][k] : RL(0.0);
+      C.col[k] = (ln < nv && k < nv) ? E.M[k][lr] : RL(0.0);
       C.dinv[k] = (k < nv) ? E.tdinv[k] : RL(1.0);
     }
   }
+  C.dl = (ln < nv) ? E.tdinv[lr] : RL(1.0);
   // uniform over the environment's lanes (its own LDS); over the wavefront only with 64 lanes
   if constexpr (L::kLanes == SIM_WAVE) fb = __builtin_amdgcn_readfirstlane(E.tfb[0] != RL(0.0) ? 1 : 0);
   else fb = (E.tfb[0] != RL(0.0)) ? 1 : 0;

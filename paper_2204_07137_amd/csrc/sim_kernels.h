@@ -366,6 +366,8 @@ __device__ __forceinline__ void window_adj_body(const WinArgs& A, int env, L& E)
 #ifdef SIM_PHASE_PROFILE
   phase_start<L::kLanes>(E.prof);
 #endif
+  // entries restore the lower triangle of the factor only; above it the block holds zeros
+  for (int i = ln; i < L::kV * (L::kV + 1); i += L::kLanes) (&E.M[0][0])[i] = RL(0.0);
   adjoint_seed(A, m, E, env, ln);
   SIM_PHASE(E, PH_A_SEED);
   // E.abar holds the adjoint of a_prev(s_h) = a_{h-1}: it seeds dL/da_{h-1}

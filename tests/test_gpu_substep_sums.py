@@ -3,6 +3,7 @@ sizes where they take another route.
 
 * The muscles' wrenches per body: along the host-made schedule up to its capacities (runs of a
   unit, slots of a pass, slots a pair of accumulators adds per pass), by atomics beyond them.
+* An environment whose state is not finite leaves the others as they are.
 """
 import numpy as np
 import pytest
@@ -68,3 +69,37 @@ def test_muscle_sums(n, runs):
     assert relnorm(_np(fw)["s_h"], ref["s_h"]) < 1e-11
     assert relnorm(ad["dL_da"], ref["dL_da"]) < 1e-9
     assert relnorm(ad["dL_ds0"], ref["dL_ds0"]) < 1e-9
+
+
+def _tree(n, free_root, N, h):
+    md = wl.models.chain(n=n, free_root=free_root, substeps=4)
+    rng = np.random.default_rng(n)
+    nq, nv, na = int(md["nq"]), int(md["nv"]), int(md["na"])
+    q = rng.uniform(-0.4, 0.4, (N, nq))
+    if free_root:
+        q[:, 3:7] = rng.normal(size=(N, 4))
+        q[:, 3:7] /= np.linalg.norm(q[:, 3:7], axis=1, keepdims=True)
+    s0 = np.concatenate([q, rng.normal(0, 0.3, (N, nv))], 1)
+    critic = [(rng.normal(size=(1, nq + nv)), np.zeros(1))]
+    return md, s0, rng.uniform(-0.5, 0.5, (h, N, na)), critic
+
+
+@pytest.mark.parametrize("n,free_root", [(1, False), (8, True), (21, True)])
+def test_a_state_that_is_not_finite(n, free_root):
+    print(f"[sums] not finite, tree of {n + 1} frames", flush=True)
+    N, h = 5, 2
+    md, s0, u, critic = _tree(n, free_root, N, h)
+    bad = s0.copy()
+    bad[2, -1] = np.inf
+    outs = []
+    for s in (s0, bad):
+        sim = P.Sim(md, N, h, None, [s0.shape[1], 1], ckpt_interval=2)
+        fw = sim.forward(s, None, critic, actions_in=u)
+        ad = sim.adjoint(fw)
+        torch.cuda.synchronize()
+        outs.append((_np(fw)["s_h"], _np(ad)["dL_ds0"]))
+    others = [0, 1, 3, 4]
+    for a, b in zip(*outs):
+        assert np.isfinite(a).all()
+        assert np.array_equal(a[others], b[others])
+        assert not np.isfinite(b[2]).all()
