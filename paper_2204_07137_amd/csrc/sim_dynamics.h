@@ -1425,12 +1425,20 @@ __device__ __forceinline__ void substep_adjoint_core(const Scal* __restrict__ m,
   wsync();
   SIM_PHASE(E, PH_A_TREESUM);
   // ---- derivatives of lambda^T ID per joint (lane = joint)
-  if (ln < J) {
-    const real* o = E.acc[ln];
+  // A FREE root's three rotations are hinges about the world axes that move with the frame itself,
+  // so they run through the hinges' code on three lanes of their own (the root's and the two past
+  // the joints) where the environment has them; by itself the root's lane spent half of this
+  // phase on them while the others waited (4.3 k cycles per humanoid substep, 2.5 k now).
+  constexpr bool ROOT_LANES = LN >= L::kJ + 2;
+  const int root_axis = (ROOT_LANES && m->floating) ? (ln == 0 ? 0 : ((ln == J || ln == J + 1) ? ln - J + 1 : -1)) : -1;
+  const bool root = root_axis >= 0;
+  if (ln < J || root) {
+    const int fr = root ? 0 : ln;
+    const real* o = E.acc[fr];
     sv P = ldsv(o + 0), Q = ldsv(o + 6), Rr = ldsv(o + 12), T = ldsv(o + 18);
     sv Fn = ldsv(o + 24), Ab = ldsv(o + 30), Vb = ldsv(o + 36);
     sv QRT = subsv(subsv(Q, Rr), T);
-    if (jr.type == J_FREE) {
+    if (!ROOT_LANES && jr.type == J_FREE) {
       int va = jr.va;
       sv vA = ldsv(E.v[ln]), wA = ldsv(E.W[ln]), aA = ldsv(E.A[ln]);
       f3 vl = mk3(E.qd[va], E.qd[va + 1], E.qd[va + 2]);
@@ -1450,22 +1458,37 @@ __device__ __forceinline__ void substep_adjoint_core(const Scal* __restrict__ m,
         E.dPqd[va + 3 + e] = dotsv(Se, QRT) - dotsv(crm(Se, vA), P) + dotsv(daS, P) + dotsv(Se, Vb);
       }
     } else {
-      sv S = ldsv(E.S[ln]);
+      const f3 ue = mk3(root_axis == 0 ? RL(1.0) : RL(0.0), root_axis == 1 ? RL(1.0) : RL(0.0),
+                        root_axis == 2 ? RL(1.0) : RL(0.0));
+      sv S = root ? mksv(ue, mk3(RL(0.0), RL(0.0), RL(0.0))) : ldsv(E.S[ln]);
       sv vA, wA, aA;
-      if (jr.par >= 0) {
-        vA = ldsv(E.v[jr.par]); wA = ldsv(E.W[jr.par]); aA = ldsv(E.A[jr.par]);
+      const int fa = root ? 0 : jr.par;   // the frame the joint turns with
+      if (fa >= 0) {
+        vA = ldsv(E.v[fa]); wA = ldsv(E.W[fa]); aA = ldsv(E.A[fa]);
       } else {
         vA = zsv(); wA = zsv(); aA = mksv(mk3(RL(0.0), RL(0.0), RL(0.0)), mk3(RL(0.0), RL(0.0), g));
       }
       sv ee = crm(S, vA);
       real val = -dotsv(crm(S, wA), Fn) - dotsv(crm(S, aA), P) - dotsv(ee, Q) + dotsv(crm(ee, vA), P) +
                   dotsv(ee, Rr) + dotsv(ee, T) + dotsv(S, Ab) - dotsv(ee, Vb);
-      if (jr.lim) {
-        real qj = E.q[jr.qa];
-        if (qj < jr.lo || qj > jr.hi) val += E.lam[jr.va] * m->klim;
+      const real eP = dotsv(ee, P), sQ = dotsv(S, QRT), sV = dotsv(S, Vb);
+      if (root) {
+        const f3 vl = mk3(E.qd[0], E.qd[1], E.qd[2]), w = mk3(E.qd[3], E.qd[4], E.qd[5]);
+        const sv Te = mksv(mk3(RL(0.0), RL(0.0), RL(0.0)), ue);
+        const sv daT = mksv(mk3(RL(0.0), RL(0.0), RL(0.0)), cross3(ue, w));
+        const sv daS = mksv(mk3(RL(0.0), RL(0.0), RL(0.0)), cross3(vl, ue));
+        E.dPq[root_axis] = dotsv(Te, Ab);
+        E.dPq[3 + root_axis] = val;
+        E.dPqd[root_axis] = dotsv(Te, QRT) - dotsv(crm(Te, vA), P) + dotsv(daT, P) + dotsv(Te, Vb);
+        E.dPqd[3 + root_axis] = sQ - eP + dotsv(daS, P) + sV;
+      } else {
+        if (jr.lim) {
+          real qj = E.q[jr.qa];
+          if (qj < jr.lo || qj > jr.hi) val += E.lam[jr.va] * m->klim;
+        }
+        E.dPq[jr.va] = val;
+        E.dPqd[jr.va] = sQ - RL(2.0) * eP + sV;
       }
-      E.dPq[jr.va] = val;
-      E.dPqd[jr.va] = dotsv(S, QRT) - RL(2.0) * dotsv(ee, P) + dotsv(S, Vb);
     }
   }
   wsync();
