@@ -21,6 +21,7 @@
 // centres of mass, inertias, mass-matrix pairs) are copied to LDS once per kernel
 struct JointRegs {
   int par, type, qa, va, depth, act, lim, npair;
+  int kids;   // children lists of the subtree sums
   unsigned int cmask;
   real lo, hi, gear, mass, arm;
 };
@@ -79,8 +80,8 @@ struct EnvLDST {
   // inertias, and the adjoint's per-body terms with their subtree sums (never live together)
   union {
     struct {
-      real F[CJ][6], Fi[CJ][6];
-      real Ic[CJ][10];
+      real FI[CJ][16];   // Newton-Euler force (6), composite inertia (10)
+      real Fi[CJ][6];
     };
     real acc[CJ][42];   // (and the third table's muscle slots)
   };
@@ -93,7 +94,6 @@ struct EnvLDST {
   real lam[CV], dPq[CV], dPqd[CV];
   // topology copies for arbitrary-index lookups
   int t_next_sib[CJ], t_type[CJ], t_va[CJ], t_parent[CJ], t_qa[CJ];
-  unsigned short t_ts[4][SIM_MAXTS] __attribute__((aligned(16)));   // subtree-sum schedule
   real arm[CV];
   real j_off[CJ][3], j_ax[CJ][3], j_com[CJ][3], j_I6[CJ][6];
   int pairs[CPAIR];
@@ -136,9 +136,8 @@ __device__ __forceinline__ void load_regs(const DevModel* __restrict__ m, L& E, 
   jr.cmask = ln < m->J ? m->cmask[j] : 0u;
   jr.arm = m->armature[m->vadr[j]];
   jr.npair = m->npair;
+  jr.kids = m->kids[j];
   for (int p = ln; p < m->npair; p += LN) E.pairs[p] = m->pair[p];
-  for (int i = ln; i < 2 * SIM_MAXTS; i += LN)
-    reinterpret_cast<unsigned int*>(&E.t_ts[0][0])[i] = reinterpret_cast<const unsigned int*>(&m->ts_edge[0][0])[i];
   for (int f = ln; f < L::kJ; f += LN) {
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
@@ -357,55 +356,43 @@ __device__ __forceinline__ double chol64_solve(L& E, int ln, double b) {
 }
 
 // --------------------------------------------------------------- subtree sums
-// Adds every frame's row of a table into its parent's row, children before parents
-// (frames are listed parents first); each active lane owns one column.  The parent index
-// is broadcast from the lane that holds it; the LDS executes one wavefront's accesses in
-// order, so a parent updated by an earlier edge is read back correctly without a wait.
-__device__ __forceinline__ void tree_sum_cols(real* col, int stride, bool active, int J, int par_reg) {
-  for (int j = J - 1; j >= 1; --j) {
-    int p = __builtin_amdgcn_readlane(par_reg, j);
-    if (active && p >= 0) col[p * stride] += col[j * stride];
-  }
-}
-
-// The forward's subtree sums of 16 columns (Newton-Euler forces, composite inertias) along
-// the model's schedule: lane = (group g of four, column c of 16); at each step every group
-// adds one frame's row into its parent's.  A step holds no edge into a frame whose own
-// incoming edges are not all done, and no two edges into one parent, so the groups touch
-// disjoint rows and the LDS performs each step's accesses after the previous step's.
-// With fewer than 64 lanes per environment a lane serves several groups, one after the
-// other within each step (the groups of a step touch disjoint rows, so the order of a step's
-// groups does not change any sum).
-template <class L>
-__device__ __forceinline__ void tree_sum_sched16(L& E, int nsteps, int ln) {
-  constexpr int LN = L::kLanes, NG = SIM_WAVE / LN;   // schedule groups per lane
-  const int c = ln & 15;
-  real* col = (c < 6) ? &E.F[0][c] : &E.Ic[0][c - 6];
-  const int st = (c < 6) ? 6 : 10;
-  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-  unsigned int w32[NG][SIM_MAXTS / 2];
+// Subtree sums: adds every frame's row of a table into its parent's row, children before parents
+// (frames are listed parents first); a lane sums one column of STRIDE-wide rows.  Most frames have
+// one child, the next frame, whose sum is still in a register when the frame's turn comes (bit of
+// `chain`); a frame with other children (bit of `multi`) reads their sums back in the order of its
+// list (first: kids >> SH, next sibling: kids >> (SH + 6), 6 bits each, 63 ends it; SH selects the
+// forward's or the adjoint's order of additions, both fixed by the model).  All rows are requested
+// at the start and every row is stored, so the sums are a chain of additions, not of LDS round
+// trips, and only a frame with a list takes a branch: a humanoid's forward sums (16 columns) take
+// 2.0 k cycles, 3.5 k as LDS additions of four edges at a time, and the adjoint's (42 columns)
+// 2.0 k, 5.0 k edge by edge.  A branch per frame instead of a select cost what the chain saved.
+// All lanes take part, because kids is read across lanes: those beyond the columns repeat another
+// lane's column and store the same values.
+template <int CJ, int STRIDE, int SH>
+__device__ __forceinline__ void tree_sum(real* col, unsigned int chain, unsigned int multi, int kids) {
+  // the masks are tested where they are used: tested ahead of the substep loop they spill
+  chain = __builtin_amdgcn_readfirstlane(chain);
+  multi = __builtin_amdgcn_readfirstlane(multi);
+  __asm__ volatile("" : "+s"(chain), "+s"(multi));
+  real x[CJ];
 #pragma unroll
-  for (int r = 0; r < NG; ++r) {
-    const int g = r * (LN / 16) + (ln >> 4);
-    const u32x4* tp = reinterpret_cast<const u32x4*>(&E.t_ts[g][0]);
+  for (int j = 0; j < CJ; ++j) x[j] = col[j * STRIDE];
+  __asm__ volatile("" ::: "memory");
+  real s = RL(0.0);
 #pragma unroll
-    for (int i = 0; i < SIM_MAXTS / 8; ++i) {
-      const u32x4 v = tp[i];
-      w32[r][4 * i] = v.x; w32[r][4 * i + 1] = v.y; w32[r][4 * i + 2] = v.z; w32[r][4 * i + 3] = v.w;
-    }
-  }
-#pragma unroll
-  for (int s = 0; s < SIM_MAXTS; ++s) {
-    if (s < nsteps) {
-#pragma unroll
-      for (int r = 0; r < NG; ++r) {
-        const unsigned int w = (w32[r][s >> 1] >> (16 * (s & 1))) & 0xffffu;
-        if (w) {
-          const int j = (int)(w & 31u), p = (int)((w >> 5) & 31u);
-          col[p * st] += col[j * st];
-        }
+  for (int j = CJ - 1; j >= 0; --j) {
+    real v = x[j];
+    const real w = v + s;
+    v = ((chain >> j) & 1u) ? w : v;
+    if (__builtin_expect((multi >> j) & 1u, 0)) {
+      int c = (__builtin_amdgcn_readlane(kids, j) >> SH) & 63;
+      while (c != 63) {
+        v += col[c * STRIDE];
+        c = (__builtin_amdgcn_readlane(kids, c) >> (SH + 6)) & 63;
       }
     }
+    col[j * STRIDE] = v;
+    s = v;
   }
 }
 
@@ -1099,7 +1086,7 @@ __device__ __forceinline__ void substep_forward(const Scal* __restrict__ m, L& E
     real Ib[10];
     body_inertia(E, jr, ln, R, p, Ib);
 #pragma unroll
-    for (int k = 0; k < 10; ++k) { E.Ib[ln][k] = Ib[k]; E.Ic[ln][k] = Ib[k]; }
+    for (int k = 0; k < 10; ++k) { E.Ib[ln][k] = Ib[k]; E.FI[ln][6 + k] = Ib[k]; }
     sv hv = iapply(Ib, v);
     sv f = addsv(iapply(Ib, ab), crf(v, hv));
     for (unsigned int cm = jr.cmask; cm; cm &= cm - 1) {
@@ -1107,7 +1094,7 @@ __device__ __forceinline__ void substep_forward(const Scal* __restrict__ m, L& E
       f = subsv(f, spf(ld3(E.cx[ci]), ld3(E.cf[ci])));
     }
     if constexpr (L::kMtu > 0) f = subsv(f, ldsv(mus_fm(E, ln)));
-    stsv(E.F[ln], f);
+    stsv(E.FI[ln], f);
     // joint torques: actuation + limit penalty
     if (jr.type != J_FREE) {
       real tau = RL(0.0);
@@ -1126,13 +1113,14 @@ __device__ __forceinline__ void substep_forward(const Scal* __restrict__ m, L& E
   wsync();
   SIM_PHASE(E, PH_F_NE);
   // ---- subtree sums of forces (6 columns) and composite inertias (10 columns)
-  tree_sum_sched16(E, m->ts_steps, ln);
+  constexpr int CJ = NV < L::kJ ? NV : L::kJ;   // a frame has at least one degree of freedom
+  tree_sum<CJ, 16, 0>(&E.FI[0][ln & 15], m->tree_chain, m->tree_multi, jr.kids);
   wsync();
   SIM_PHASE(E, PH_F_TREESUM);
   // ---- bias into rhs; composite-inertia columns F_i = Ic_i S_i; root block of M
   if (ln < J) {
-    sv F = ldsv(E.F[ln]);
-    const real* Ic = E.Ic[ln];
+    sv F = ldsv(E.FI[ln]);
+    const real* Ic = E.FI[ln] + 6;
     if (jr.type == J_FREE) {
       int va = jr.va;
       E.vec[va + 0] -= F.l.x; E.vec[va + 1] -= F.l.y; E.vec[va + 2] -= F.l.z;
@@ -1417,10 +1405,11 @@ __device__ __forceinline__ void substep_adjoint_core(const Scal* __restrict__ m,
   wsync();
   SIM_PHASE(E, PH_A_BODY);
   // one lane per column of the 42 (several passes with fewer than 42 lanes per environment)
+  constexpr int CJ = NV < L::kJ ? NV : L::kJ;
 #pragma unroll
   for (int c0 = 0; c0 < 42; c0 += LN) {
     const int c = c0 + ln;
-    tree_sum_cols(&E.acc[0][c < 42 ? c : 0], 42, c < 42, J, jr.par);
+    tree_sum<CJ, 42, 12>(&E.acc[0][c < 42 ? c : 41], m->tree_chain, m->tree_multi, jr.kids);
   }
   wsync();
   SIM_PHASE(E, PH_A_TREESUM);

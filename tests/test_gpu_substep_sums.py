@@ -3,6 +3,8 @@ sizes where they take another route.
 
 * The muscles' wrenches per body: along the host-made schedule up to its capacities (runs of a
   unit, slots of a pass, slots a pair of accumulators adds per pass), by atomics beyond them.
+* The subtree sums, the triangular solves and the FREE root's rotation columns: trees of two to
+  32 frames whose frames have one child, several or none, at every size class of the mass matrix.
 * An environment whose state is not finite leaves the others as they are.
 """
 import numpy as np
@@ -82,6 +84,24 @@ def _tree(n, free_root, N, h):
     s0 = np.concatenate([q, rng.normal(0, 0.3, (N, nv))], 1)
     critic = [(rng.normal(size=(1, nq + nv)), np.zeros(1))]
     return md, s0, rng.uniform(-0.5, 0.5, (h, N, na)), critic
+
+
+@pytest.mark.parametrize("n,free_root", [(1, False), (1, True), (2, True), (8, True), (9, True), (13, False),
+                                         (21, True), (26, True), (31, False)])
+def test_trees(n, free_root):
+    """Tolerances: those of the 152-muscle humanoid's short window."""
+    print(f"[sums] tree of {n + 1} frames, free root {free_root}", flush=True)
+    N, h = 3, 2
+    md, s0, u, critic = _tree(n, free_root, N, h)
+    ref = oracle_window_grads(md, s0, h, None, critic, actions=u, n_total=N)
+    for kw in (dict(ckpt_interval=2), dict(path=P.PATH_TAPE), dict(ckpt_interval=2, factor_cache=True)):
+        sim = P.Sim(md, N, h, None, [s0.shape[1], 1], precision="fp64", **kw)
+        fw = sim.forward(s0, None, critic, actions_in=u)
+        ad = _np(sim.adjoint(fw))
+        torch.cuda.synchronize()
+        assert relnorm(_np(fw)["s_h"], ref["s_h"]) < 1e-10, kw
+        assert relnorm(ad["dL_da"], ref["dL_da"]) < 1e-8, kw
+        assert relnorm(ad["dL_ds0"], ref["dL_ds0"]) < 1e-8, kw
 
 
 @pytest.mark.parametrize("n,free_root", [(1, False), (8, True), (21, True)])
