@@ -554,6 +554,7 @@ __device__ __forceinline__ void muscle_wrenches(const Scal* __restrict__ m, L& E
 #pragma unroll
   for (int r = 0; r < SIM_MUS_RF; ++r) sum[r] = RL(0.0);
   SIM_PHASE(E, PH_F_MUSCLE);
+  ln = relane<SIM_MAXV>(ln);
   for (int i0 = 0; i0 < m->n_mtu; i0 += SIM_WAVE) {
     const int i = i0 + ln, p = i0 / SIM_WAVE;
     // the pass's schedule is requested before its paths are formed
@@ -680,6 +681,7 @@ __device__ __forceinline__ void muscle_adjoint(const Scal* __restrict__ m, L& E,
   real* mab = &E.mus[(SIM_MUS_CA + cp) * SIM_MUS_STRIDE];
   real* mvb = &E.mus[(2 * SIM_MUS_CA + cp) * SIM_MUS_STRIDE];
   SIM_PHASE(E, PH_A_MUSCLE);
+  ln = relane<SIM_MAXV>(ln);
   for (int i0 = 0; i0 < m->n_mtu; i0 += SIM_WAVE) {
     const int i = i0 + ln, p = i0 / SIM_WAVE;
     constexpr int PRE = 3;   // chunks of the schedule requested before the paths are formed
@@ -850,7 +852,7 @@ __device__ __forceinline__ void muscle_adjoint(const Scal* __restrict__ m, L& E,
 // besides the factor and the accelerations): reference point, joint rotations, frame
 // transforms, screws, velocities and bias accelerations, contact forces.  Leaves the lane's
 // frame rotation and position in R, p and its screw, velocity and bias acceleration in S, v, ab.
-template <class L>
+template <int NV, class L>
 __device__ __forceinline__ void substep_kin(const Scal* __restrict__ m, L& E, const JointRegs& jr,
                                             const ContactRegs& cr, int ln, real* R, f3& p, sv& S, sv& v, sv& ab) {
   constexpr int LN = L::kLanes;
@@ -925,6 +927,7 @@ __device__ __forceinline__ void substep_kin(const Scal* __restrict__ m, L& E, co
     }
   }
   SIM_PHASE(E, PH_F_FK);
+  ln = relane<NV>(ln);
   // motion subspaces: a hinge turns about its own axis, so its world axis is R ax either
   // side of the joint rotation; a slide keeps the parent's rotation
   sv u = zsv(), c = zsv();
@@ -976,6 +979,7 @@ __device__ __forceinline__ void substep_kin(const Scal* __restrict__ m, L& E, co
   }
   wsync();
   SIM_PHASE(E, PH_F_VEL);
+  ln = relane<NV>(ln);
   // ---- contacts (lane = contact)
   bool adh = false;
   if (ln < nc) {
@@ -1000,6 +1004,7 @@ __device__ __forceinline__ void substep_kin(const Scal* __restrict__ m, L& E, co
   }
   wsync();
   SIM_PHASE(E, PH_F_CONTACT);
+  ln = relane<NV>(ln);
 }
 
 // The world spatial inertia (10 numbers) of the lane's body from its frame R, p.
@@ -1076,7 +1081,7 @@ __device__ __forceinline__ void substep_forward(const Scal* __restrict__ m, L& E
   real R[9];
   f3 p;
   sv S, v, ab;
-  substep_kin(m, E, jr, cr, ln, R, p, S, v, ab);
+  substep_kin<NV>(m, E, jr, cr, ln, R, p, S, v, ab);
   if constexpr (L::kMtu > 0) {
     muscle_wrenches(m, E, ln);
     SIM_PHASE(E, PH_F_MUSCLE);
@@ -1112,11 +1117,13 @@ __device__ __forceinline__ void substep_forward(const Scal* __restrict__ m, L& E
   }
   wsync();
   SIM_PHASE(E, PH_F_NE);
+  ln = relane<NV>(ln);
   // ---- subtree sums of forces (6 columns) and composite inertias (10 columns)
   constexpr int CJ = NV < L::kJ ? NV : L::kJ;   // a frame has at least one degree of freedom
   tree_sum<CJ, 16, 0>(&E.FI[0][ln & 15], m->tree_chain, m->tree_multi, jr.kids);
   wsync();
   SIM_PHASE(E, PH_F_TREESUM);
+  ln = relane<NV>(ln);
   // ---- bias into rhs; composite-inertia columns F_i = Ic_i S_i; root block of M
   if (ln < J) {
     sv F = ldsv(E.FI[ln]);
@@ -1153,6 +1160,7 @@ __device__ __forceinline__ void substep_forward(const Scal* __restrict__ m, L& E
   }
   wsync();
   SIM_PHASE(E, PH_F_BIAS);
+  ln = relane<NV>(ln);
   // ---- CRBA entries M[va_k][va_i] = S_k . F_i, one (frame, ancestor) pair per lane and round
   for (int r = 0; r * LN < jr.npair; ++r) {
     int pi = r * LN + ln;
@@ -1175,6 +1183,7 @@ __device__ __forceinline__ void substep_forward(const Scal* __restrict__ m, L& E
   }
   wsync();
   SIM_PHASE(E, PH_F_CRBA);
+  ln = relane<NV>(ln);
   // ---- Cholesky and solve (lane = DOF); rows >= nv padded with the identity
   if (nv == NV) {
     // no padding: the lanes past the matrix read row 0; no lane of the matrix reads them back
@@ -1193,6 +1202,7 @@ __device__ __forceinline__ void substep_forward(const Scal* __restrict__ m, L& E
   real b = ln < nv ? E.vec[ln] : RL(0.0);
   real x;
   SIM_PHASE(E, PH_F_CHOL);
+  ln = relane<NV>(ln);
   if (fb) {
     chol64_factor<NV>(E, nv, ln);
     SIM_PHASE(E, PH_F_FACTOR);
@@ -1222,6 +1232,7 @@ __device__ __forceinline__ void substep_forward(const Scal* __restrict__ m, L& E
   }
   wsync();
   SIM_PHASE(E, PH_F_SOLVE);
+  ln = relane<NV>(ln);
   integrate_positions(m, E, jr, ln);
   wsync();
   if (inplace) {
@@ -1232,18 +1243,19 @@ __device__ __forceinline__ void substep_forward(const Scal* __restrict__ m, L& E
     wsync();
   }
   SIM_PHASE(E, PH_F_INTEG);
+  ln = relane<NV>(ln);
 }
 
 // What the reverse of a substep reads of its forward when the factor and the accelerations
 // come from the factor cache: the kinematics, the contacts and the body inertias of the
 // pre-substep state, computed by the forward's own code.
-template <class L>
+template <int NV, class L>
 __device__ __forceinline__ void substep_kinematics(const Scal* __restrict__ m, L& E, const JointRegs& jr,
                                                    const ContactRegs& cr, int ln) {
   real R[9];
   f3 p;
   sv S, v, ab;
-  substep_kin(m, E, jr, cr, ln, R, p, S, v, ab);
+  substep_kin<NV>(m, E, jr, cr, ln, R, p, S, v, ab);
   if (ln < m->J) {
     real Ib[10];
     body_inertia(E, jr, ln, R, p, Ib);
@@ -1307,6 +1319,7 @@ __device__ __forceinline__ void substep_adjoint_core(const Scal* __restrict__ m,
   }
   wsync();
   SIM_PHASE(E, PH_A_INTEG);
+  ln = relane<NV>(ln);
   // ---- lambda = M^{-1} qdd_bar with the cached factor (lane = DOF)
   {
     real rb = ln < nv ? dt * E.qdb[ln] : RL(0.0);
@@ -1315,6 +1328,7 @@ __device__ __forceinline__ void substep_adjoint_core(const Scal* __restrict__ m,
   }
   wsync();
   SIM_PHASE(E, PH_A_LAMBDA);
+  ln = relane<NV>(ln);
   // actuation adjoint and full accelerations / virtual velocities
   if (ln < J && jr.act >= 0) E.abar[jr.act] += jr.gear * E.lam[jr.va];
   // local terms (lane = joint), then their sums along each root path by pointer jumping
@@ -1346,6 +1360,7 @@ __device__ __forceinline__ void substep_adjoint_core(const Scal* __restrict__ m,
   }
   wsync();
   SIM_PHASE(E, PH_A_PATH);
+  ln = relane<NV>(ln);
   // ---- contact adjoints (lane = contact)
   if (ln < nc) {
     int b = cr.body;
@@ -1372,6 +1387,7 @@ __device__ __forceinline__ void substep_adjoint_core(const Scal* __restrict__ m,
   }
   wsync();
   SIM_PHASE(E, PH_A_CONTACT);
+  ln = relane<NV>(ln);
   if constexpr (L::kMtu > 0) {
     muscle_adjoint(m, E, ln);
     SIM_PHASE(E, PH_A_MUSCLE);
@@ -1404,6 +1420,7 @@ __device__ __forceinline__ void substep_adjoint_core(const Scal* __restrict__ m,
   }
   wsync();
   SIM_PHASE(E, PH_A_BODY);
+  ln = relane<NV>(ln);
   // one lane per column of the 42 (several passes with fewer than 42 lanes per environment)
   constexpr int CJ = NV < L::kJ ? NV : L::kJ;
 #pragma unroll
@@ -1413,6 +1430,7 @@ __device__ __forceinline__ void substep_adjoint_core(const Scal* __restrict__ m,
   }
   wsync();
   SIM_PHASE(E, PH_A_TREESUM);
+  ln = relane<NV>(ln);
   // ---- derivatives of lambda^T ID per joint (lane = joint)
   // A FREE root's three rotations are hinges about the world axes that move with the frame itself,
   // so they run through the hinges' code on three lanes of their own (the root's and the two past
@@ -1482,6 +1500,7 @@ __device__ __forceinline__ void substep_adjoint_core(const Scal* __restrict__ m,
   }
   wsync();
   SIM_PHASE(E, PH_A_DERIV);
+  ln = relane<NV>(ln);
   // ---- adjoint of the pre-substep state
   if (ln < nv) E.qdb[ln] -= E.dPqd[ln];
   if (ln < J) {
@@ -1505,6 +1524,7 @@ __device__ __forceinline__ void substep_adjoint_core(const Scal* __restrict__ m,
   }
   wsync();
   SIM_PHASE(E, PH_A_STATE);
+  ln = relane<NV>(ln);
 }
 
 // Adjoint of one substep from its pre-state alone: the forward linearisation is

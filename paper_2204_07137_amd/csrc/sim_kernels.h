@@ -161,7 +161,7 @@ template <int NV, class L, int PATH = KP_ANY>
 __device__ __forceinline__ void window_fwd_body(const WinArgs& A, int env, L& E) {
   const Scal scl = load_scal(A.model);
   const Scal* m = &scl;
-  const int ln = grp_lane<L::kLanes>();
+  int ln = grp_lane<L::kLanes>();
   JointRegs jr;
   ContactRegs cr;
   load_regs(A.model, E, ln, jr, cr);
@@ -179,6 +179,7 @@ __device__ __forceinline__ void window_fwd_body(const WinArgs& A, int env, L& E)
     frame_begin(A, m, E, env, t, ln);
     SIM_PHASE(E, PH_FRAME_BEGIN);
     for (int sub = 0; sub < S; ++sub) {
+      ln = relane<NV>(ln);
       int gi = t * S + sub;
       int fb;
       if (PATH == KP_TAPE || (PATH == KP_ANY && A.tape_full)) {
@@ -355,7 +356,7 @@ __device__ __forceinline__ void window_adj_body(const WinArgs& A, int env, L& E)
   const bool use_fc = L::kMtu == 0 && (PATH == KP_FC || (PATH == KP_ANY && A.fc));
   const Scal scl = load_scal(A.model);
   const Scal* m = &scl;
-  const int ln = grp_lane<L::kLanes>();
+  int ln = grp_lane<L::kLanes>();
   JointRegs jr;
   ContactRegs cr;
   load_regs(A.model, E, ln, jr, cr);
@@ -399,6 +400,7 @@ __device__ __forceinline__ void window_adj_body(const WinArgs& A, int env, L& E)
       TapeRegs<L> P;
       tape_prefetch<L>(TM, P, A.tape + (((size_t)t * S + S - 1) * N + env) * A.tape_ws, ln);
       for (int sub = S - 1; sub >= 0; --sub) {
+        ln = relane<NV>(ln);
         int fb;
         tape_load_regs<NV>(m, TM, E, C, fb, ln, P);
         if (sub > 0) tape_prefetch<L>(TM, P, A.tape + (((size_t)t * S + sub - 1) * N + env) * A.tape_ws, ln);
@@ -421,6 +423,7 @@ __device__ __forceinline__ void window_adj_body(const WinArgs& A, int env, L& E)
         FP.qd = (ln < nv) ? E.qd[ln] : RL(0.0);
         SIM_PHASE(E, PH_FC_STATES);
         for (int i = k - 1; i >= 0; --i) {
+          ln = relane<NV>(ln);
           int fb;
           fc_load_regs(m, FM, E, fb, ln, FP);
           if (i > 0) {
@@ -436,7 +439,7 @@ __device__ __forceinline__ void window_adj_body(const WinArgs& A, int env, L& E)
             substep_forward<NV>(m, E, jr, cr, ln, C, false, fb);
           } else {
             // the factor enters registers only now: it is not live across the kinematics
-            substep_kinematics(m, E, jr, cr, ln);
+            substep_kinematics<NV>(m, E, jr, cr, ln);
             int fb2;
             factor_from_block<NV>(m, E, C, fb2, ln);
             SIM_PHASE(E, PH_TAPE_LOAD);
@@ -454,6 +457,7 @@ __device__ __forceinline__ void window_adj_body(const WinArgs& A, int env, L& E)
         // recompute the segment from its checkpoint, recording pre-states and
         // linearisations; the last substep's linearisation stays on chip
         for (int i = 0; i < k - 1; ++i) {
+          ln = relane<NV>(ln);
           int fb;
           substep_forward<NV>(m, E, jr, cr, ln, C, false, fb);
           tape_store<NV>(TM, E, C, fb, ln, tseg + (size_t)i * A.tape_ws);
@@ -469,6 +473,7 @@ __device__ __forceinline__ void window_adj_body(const WinArgs& A, int env, L& E)
           substep_adjoint_core<NV>(m, E, jr, cr, ln, C, fb);
         }
         for (int i = k - 2; i >= 0; --i) {
+          ln = relane<NV>(ln);
           int fb;
           tape_load_regs<NV>(m, TM, E, C, fb, ln, P);
           if (i > 0) tape_prefetch<L>(TM, P, tseg + (size_t)(i - 1) * A.tape_ws, ln);
