@@ -366,14 +366,17 @@ __device__ __forceinline__ double chol64_solve(L& E, int ln, double b) {
 // trips, and only a frame with a list takes a branch: a humanoid's forward sums (16 columns) take
 // 2.0 k cycles, 3.5 k as LDS additions of four edges at a time, and the adjoint's (42 columns)
 // 2.0 k, 5.0 k edge by edge.  A branch per frame instead of a select cost what the chain saved.
-// All lanes take part, because kids is read across lanes: those beyond the columns repeat another
-// lane's column and store the same values.
-template <int CJ, int STRIDE, int SH>
+// All lanes of an environment take part, because kids is read across lanes: those beyond the
+// columns repeat another lane's column and store the same values.  kids is read from the first
+// active environment of the wavefront (all hold the same model): where environments share a
+// wavefront, only some of them may recompute a substep.
+template <int CJ, int STRIDE, int SH, int LN>
 __device__ __forceinline__ void tree_sum(real* col, unsigned int chain, unsigned int multi, int kids) {
   // the masks are tested where they are used: tested ahead of the substep loop they spill
   chain = __builtin_amdgcn_readfirstlane(chain);
   multi = __builtin_amdgcn_readfirstlane(multi);
   __asm__ volatile("" : "+s"(chain), "+s"(multi));
+  const int base = LN == SIM_WAVE ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x) & (SIM_WAVE - LN);
   real x[CJ];
 #pragma unroll
   for (int j = 0; j < CJ; ++j) x[j] = col[j * STRIDE];
@@ -385,10 +388,10 @@ __device__ __forceinline__ void tree_sum(real* col, unsigned int chain, unsigned
     const real w = v + s;
     v = ((chain >> j) & 1u) ? w : v;
     if (__builtin_expect((multi >> j) & 1u, 0)) {
-      int c = (__builtin_amdgcn_readlane(kids, j) >> SH) & 63;
+      int c = (__builtin_amdgcn_readlane(kids, base + j) >> SH) & 63;
       while (c != 63) {
         v += col[c * STRIDE];
-        c = (__builtin_amdgcn_readlane(kids, c) >> (SH + 6)) & 63;
+        c = (__builtin_amdgcn_readlane(kids, base + c) >> (SH + 6)) & 63;
       }
     }
     col[j * STRIDE] = v;
@@ -1120,7 +1123,7 @@ __device__ __forceinline__ void substep_forward(const Scal* __restrict__ m, L& E
   ln = relane<NV>(ln);
   // ---- subtree sums of forces (6 columns) and composite inertias (10 columns)
   constexpr int CJ = NV < L::kJ ? NV : L::kJ;   // a frame has at least one degree of freedom
-  tree_sum<CJ, 16, 0>(&E.FI[0][ln & 15], m->tree_chain, m->tree_multi, jr.kids);
+  tree_sum<CJ, 16, 0, L::kLanes>(&E.FI[0][ln & 15], m->tree_chain, m->tree_multi, jr.kids);
   wsync();
   SIM_PHASE(E, PH_F_TREESUM);
   ln = relane<NV>(ln);
@@ -1426,7 +1429,7 @@ __device__ __forceinline__ void substep_adjoint_core(const Scal* __restrict__ m,
 #pragma unroll
   for (int c0 = 0; c0 < 42; c0 += LN) {
     const int c = c0 + ln;
-    tree_sum<CJ, 42, 12>(&E.acc[0][c < 42 ? c : 41], m->tree_chain, m->tree_multi, jr.kids);
+    tree_sum<CJ, 42, 12, LN>(&E.acc[0][c < 42 ? c : 41], m->tree_chain, m->tree_multi, jr.kids);
   }
   wsync();
   SIM_PHASE(E, PH_A_TREESUM);

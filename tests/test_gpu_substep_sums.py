@@ -5,7 +5,8 @@ sizes where they take another route.
   unit, slots of a pass, slots a pair of accumulators adds per pass), by atomics beyond them.
 * The subtree sums, the triangular solves and the FREE root's rotation columns: trees of two to
   32 frames whose frames have one child, several or none, at every size class of the mass matrix.
-* An environment whose state is not finite leaves the others as they are.
+* An environment whose state is not finite, or that recomputes a substep, leaves the others of its
+  wavefront as they are.
 """
 import numpy as np
 import pytest
@@ -123,3 +124,40 @@ def test_a_state_that_is_not_finite(n, free_root):
         assert np.isfinite(a).all()
         assert np.array_equal(a[others], b[others])
         assert not np.isfinite(b[2]).all()
+
+
+@pytest.mark.parametrize("lanes", [32, 16])
+@pytest.mark.parametrize("form", [dict(path=P.PATH_TAPE), dict(ckpt_interval=4, factor_cache=True)])
+def test_environments_of_a_wavefront_that_recompute_apart(lanes, form):
+    """Stored substeps that fell back to FP64 are recomputed by the adjoint, and only by the
+    environments concerned: a threshold at which some of a wavefront's environments fall back and
+    others do not must leave every result as one environment per wavefront gives it."""
+    print(f"[sums] ant, {lanes} lanes, {form}", flush=True)
+    N, h = 8, 2
+    W = wl.workload("ant", N)
+    od = W["obs_dim"]
+    dims = [od] + [w.shape[0] for w, _ in W["actor"]], [od] + [w.shape[0] for w, _ in W["critic"]]
+
+    def run(thr, lanes_per_env):
+        sim = P.Sim(W["model"], N, h, *dims, lanes_per_env=lanes_per_env, chol_fp64_threshold=thr, **form)
+        fw = sim.forward(W["s0"], W["actor"], W["critic"])
+        ad = sim.adjoint(fw)
+        torch.cuda.synchronize()
+        return _np(fw), _np(ad)
+
+    total = h * int(W["model"]["substeps"])
+    # bisect for a threshold at which about half of all substeps fall back
+    lo, hi = 1e-7, 1.0
+    for _ in range(40):
+        thr = float(np.sqrt(lo * hi))
+        fw, ad = run(thr, 0)
+        count = fw["fp64_refactor_count"]
+        if (np.abs(np.diff(count)) > 0).sum() >= 4:
+            break
+        lo, hi = (thr, hi) if count.sum() < N * total / 2 else (lo, thr)
+    assert (np.abs(np.diff(count)) > 0).sum() >= 4, "no threshold separates the environments"
+    fc, ac = run(thr, lanes)
+    for key in ("s_h", "rewards", "value", "fp64_refactor_count"):
+        assert np.array_equal(fw[key], fc[key]), key
+    for key in ("dL_da", "dL_ds0"):
+        assert np.array_equal(ad[key], ac[key]), key
