@@ -364,7 +364,7 @@ __device__ __forceinline__ double chol64_solve(L& E, int ln, double b) {
 // forward's or the adjoint's order of additions, both fixed by the model).  All rows are requested
 // at the start and every row is stored, so the sums are a chain of additions, not of LDS round
 // trips, and only a frame with a list takes a branch: a humanoid's forward sums (16 columns) take
-// 2.0 k cycles, 3.5 k as LDS additions of four edges at a time, and the adjoint's (42 columns)
+// 2.2 k cycles, 3.5 k as LDS additions of four edges at a time, and the adjoint's (42 columns)
 // 2.0 k, 5.0 k edge by edge.  A branch per frame instead of a select cost what the chain saved.
 // All lanes of an environment take part, because kids is read across lanes: those beyond the
 // columns repeat another lane's column and store the same values.  kids is read from the first
