@@ -1046,19 +1046,20 @@ static void launch_wgrad(WgradArgs& g, const ThetaArgsT<real>& T, hipStream_t s)
   hipLaunchKernelGGL(k_mlp_wgrad, dim3((unsigned)(WG_XCD * tb * zs)), dim3(MR_THREADS), 0, s, g);
 }
 
+// every field but the step's own (a caller may use Q again for a minibatch that takes another
+// route): the gain / bias sums lie apart from the partial gradients or among them
 static void reduce_args(ReduceArgs& Q, const ThetaArgsT<real>& T, const real* part, int splits, int ln_blocks, bool ln_apart) {
+  const bool apart = T.ln && ln_apart;
   Q.part = part;
   Q.splits = splits;
   Q.np = mlp_params(T);
-  if (T.ln && ln_apart) {
-    Q.lnpart = T.lnpart;
-    Q.lnw = mlp_ln_width(T);
-    Q.ln_blocks = ln_blocks;
-    Q.og1 = T.off_g[0];
-    Q.n1 = 2 * T.dims[1];
-    Q.og2 = T.nl > 2 ? T.off_g[1] : 0;
-    Q.n2 = T.nl > 2 ? 2 * T.dims[2] : 0;
-  }
+  Q.lnpart = apart ? T.lnpart : nullptr;
+  Q.lnw = apart ? mlp_ln_width(T) : 0;
+  Q.ln_blocks = apart ? ln_blocks : 0;
+  Q.og1 = apart ? T.off_g[0] : 0;
+  Q.n1 = apart ? 2 * T.dims[1] : 0;
+  Q.og2 = apart && T.nl > 2 ? T.off_g[1] : 0;
+  Q.n2 = apart && T.nl > 2 ? 2 * T.dims[2] : 0;
 }
 
 int launch_theta(const ThetaArgsT<real>& T, void* stream) {
