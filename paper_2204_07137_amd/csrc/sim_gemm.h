@@ -336,10 +336,10 @@ __device__ __forceinline__ void rows_input(const MlpNet& N, const int* perm, lon
   }
 }
 
-// the linear output of a critic, V = w . x + b: TP lanes a row, every one gets it
+// the linear output of a critic for row r, V = w . x + b: TP lanes a row, every one gets it
 template <int TP>
-__device__ __forceinline__ real rows_output(const real* cur, int ld, const real* w, const real* b, int K) {
-  const int r = threadIdx.x / TP, p = threadIdx.x % TP;
+__device__ __forceinline__ real rows_output(const real* cur, int ld, const real* w, const real* b, int K, int r) {
+  const int p = threadIdx.x % TP;
   real s = RL(0.0);
   for (int k = p; k < K; k += TP) s = m_fma(cur[r * ld + k], w[k], s);
 #pragma unroll
@@ -423,13 +423,13 @@ __global__ __launch_bounds__(MR_THREADS, rows_waves(RT, MODE, LN)) void k_mlp_ro
       if (L > 1) forward(0, N.W0, N.b0, N.d0, N.d1, N.H1, N.g1, N.be1, N.Y1);
       if (L > 2) forward(1, N.W1, N.b1, N.d1, N.d2, N.H2, N.g2, N.be2, N.Y2);
       {
-        // (a block of 48 rows leaves the lanes past them idle)
+        // (in a block of 48 rows the lanes past them repeat the last row)
         constexpr int TP = RT == 1 ? 16 : (RT == 2 ? 8 : 4);
         const int r = (tid / TP < R) ? tid / TP : R - 1, p = tid % TP;
         const real* cur = lds + ((L - 1) & 1) * R * ld;
         real* nxt = lds + (L & 1) * R * ld;
         const real V = rows_output<TP>(cur, ld, L == 1 ? N.W0 : (L == 2 ? N.W1 : N.W2), L == 1 ? N.b0 : (L == 2 ? N.b1 : N.b2),
-                                      net_dim(N, L - 1));
+                                      net_dim(N, L - 1), r);
         if constexpr (MODE == ROWS_VALUES) {
           if (p == 0 && tid / TP < rows) g.V[m0 + r] = V;
         } else {
@@ -646,7 +646,7 @@ __global__ __launch_bounds__(FIT_WAVES * SIM_WAVE) void k_mlp_fit(FitArgs g) {
   const int ldt = L == 1 ? g.ld0 : (L == 2 ? g.ld1 : g.ld2), dtop = L == 1 ? N.d0 : (L == 2 ? N.d1 : N.d2);
   {
     const int r = tid / TP, p = tid % TP;
-    const real V = rows_output<TP>(top, ldt, L == 1 ? N.W0 : (L == 2 ? N.W1 : N.W2), L == 1 ? N.b0 : (L == 2 ? N.b1 : N.b2), dtop);
+    const real V = rows_output<TP>(top, ldt, L == 1 ? N.W0 : (L == 2 ? N.W1 : N.W2), L == 1 ? N.b0 : (L == 2 ? N.b1 : N.b2), dtop, r);
     real d = RL(0.0), s2 = RL(0.0);
     if (r < rows) {
       const real err = V - yr;

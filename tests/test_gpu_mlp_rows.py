@@ -127,3 +127,14 @@ def test_policy_gradient(hidden, layer_norm, precision, tol):
         grads = torch.autograd.grad(a, params, ad["dL_da"].double().cpu().reshape(-1, 1))
         assert rel(ad["dL_dtheta_flat"], torch.cat([g.reshape(-1) for g in grads])) < tol
         sim.close()
+
+
+# one hidden layer: the input of the output layer is the last of a tile's LDS
+@pytest.mark.parametrize("precision,tol", [("fp64", 1e-12), ("fp32", 1e-5)])
+@pytest.mark.parametrize("hidden", [[64], [128]])
+@pytest.mark.parametrize("rows", [32769, 36864])
+def test_values_of_48_row_tiles(rows, hidden, precision, tol):
+    print(f"[mlp_rows] values {hidden} {precision} rows={rows}", flush=True)
+    sim, net, _ = _critic(hidden, False, precision)
+    x, _ = _inputs(rows)
+    assert rel(sim.critic_values(x, _put(net, sim.dtype)), OL.critic_values(net, x, None)) < tol
