@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <memory>
 #include <mutex>
 #include <string>
@@ -1573,17 +1574,30 @@ static int learn_launch(float, const LearnAdamT<float>& A, void* s) { return sim
 static int learn_launch(double, const LearnAdamT<double>& A, void* s) { return sim_l64::launch_adam(A, s); }
 static int soft_launch(const SoftUpdateT<float>& A, void* s) { return sim_l32::launch_soft_update(A, s); }
 static int soft_launch(const SoftUpdateT<double>& A, void* s) { return sim_l64::launch_soft_update(A, s); }
+// One launch over the list, whose elements the kernel takes in any order; a tensor that shares
+// memory with an earlier one, where one of the two is written, begins a launch of its own, so that
+// the list is worked off in its order as far as that shows.
 template <typename T>
 static int soft_impl(void* const* target, const void* const* online, const size_t* sizes, int n, double alpha, void* s) {
   SoftUpdateT<T> A;
   std::memset(&A, 0, sizeof(A));
-  A.n = n;
-  for (int i = 0; i < n; ++i) {
-    A.t[i] = static_cast<T*>(target[i]);
-    A.o[i] = static_cast<const T*>(online[i]);
-    A.size[i] = (long)sizes[i];
-  }
   A.alpha = (T)alpha;
+  auto shared = [](const T* a, long na, const T* b, long nb) { return std::less<const T*>()(a, b + nb) && std::less<const T*>()(b, a + na); };
+  for (int i = 0; i < n; ++i) {
+    T* t = static_cast<T*>(target[i]);
+    const T* o = static_cast<const T*>(online[i]);
+    const long m = (long)sizes[i];
+    bool own = false;
+    for (int k = 0; k < A.n; ++k)
+      own = own || shared(t, m, A.t[k], A.size[k]) || shared(t, m, A.o[k], A.size[k]) || shared(o, m, A.t[k], A.size[k]);
+    if (own) {
+      if (soft_launch(A, s)) return -1;
+      A.n = 0;
+    }
+    A.t[A.n] = t;
+    A.o[A.n] = o;
+    A.size[A.n++] = m;
+  }
   return soft_launch(A, s);
 }
 static int td_launch(const float* r, const float* v, const uint8_t* d, int h, int N, double g, double l, float* out,

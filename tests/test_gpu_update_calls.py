@@ -53,3 +53,17 @@ def test_soft_update_lists(n):
     P.soft_update(t, o, 0.995)
     for a, b in zip(t, want):
         assert rel(a, b) < 1e-15
+
+
+def test_soft_update_takes_a_list_in_its_order():
+    """A list may hand a network on (b follows a, then c follows b) or name a tensor twice."""
+    g = torch.Generator().manual_seed(3)
+    a, b, c = (torch.randn(300001, generator=g, dtype=torch.float64).cuda() for _ in range(3))
+    mix = lambda x, y: 0.25 * x + 0.75 * y
+    b1 = mix(b.cpu(), a.cpu())
+    c1 = mix(c.cpu(), b1)
+    c2 = mix(c1, a.cpu())
+    tail = mix(c2[1000:], b1[1000:])
+    P.soft_update([b, c, c, c[1000:]], [a, b, a, b[1000:]], 0.25)
+    assert rel(b, b1) < 1e-15
+    assert rel(c, torch.cat([c2[:1000], tail])) < 1e-15
