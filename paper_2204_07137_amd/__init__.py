@@ -676,6 +676,13 @@ def _stream():
     return _p(torch.cuda.current_stream().cuda_stream)
 
 
+def _capturing():
+    """Whether the current stream is being captured into a graph.  Nothing is allocated then: a
+    replay would write to scratch that the allocator has long given away."""
+    import torch
+    return torch.cuda.is_current_stream_capturing()
+
+
 def adam_step(params, grad, m, v, step, lr, beta1=0.7, beta2=0.95, eps=1e-8):
     """sim_adam_step: one Adam step on a list of device tensors whose gradient and moments are
     the flat tensors grad, m, v (in list order); m and v are updated in place."""
@@ -711,18 +718,23 @@ def td_lambda(rewards, values, gamma=0.99, lam=0.95, done=None):
 
 
 def obs_stats_update(obs, count, mean, var, inv_std, eps=1e-5):
-    """sim_obs_stats_update_ws: merges obs [rows, dim] (device) into the running statistics
+    """sim_obs_stats_update, large batches by sim_obs_stats_update_ws: merges obs [rows, dim] (device) into the running statistics
     (count, mean [dim], var [dim]) in place, writes inv_std = 1 / sqrt(var + eps), and
     returns the new count."""
     obs = obs.reshape(-1, mean.numel())
     assert obs.is_contiguous() and all(x.dtype == obs.dtype and x.is_cuda for x in (mean, var, inv_std))
     rows, dim = obs.shape
-    # scratch from torch's allocator: ordered on the current stream, like the kernels
-    nb = int(lib().sim_obs_stats_workspace_bytes(rows, dim))
-    ws = obs.new_empty(nb // obs.element_size())
-    _check(lib().sim_obs_stats_update_ws(_p(obs.data_ptr()), rows, dim, float(count), _p(mean.data_ptr()),
+    L = lib()
+    if rows >= 1024 and not _capturing():
+        # scratch from torch's allocator: ordered on the current stream, like the kernels
+        nb = int(L.sim_obs_stats_workspace_bytes(rows, dim))
+        ws = obs.new_empty(nb // obs.element_size())
+        _check(L.sim_obs_stats_update_ws(_p(obs.data_ptr()), rows, dim, float(count), _p(mean.data_ptr()),
                                          _p(var.data_ptr()), _p(inv_std.data_ptr()), float(eps), _prec(obs),
                                          _p(ws.data_ptr()), nb, _stream()))
+    else:
+        _check(L.sim_obs_stats_update(_p(obs.data_ptr()), rows, dim, float(count), _p(mean.data_ptr()),
+                                      _p(var.data_ptr()), _p(inv_std.data_ptr()), float(eps), _prec(obs), _stream()))
     return count + rows
 
 

@@ -67,3 +67,29 @@ def test_soft_update_takes_a_list_in_its_order():
     P.soft_update([b, c, c, c[1000:]], [a, b, a, b[1000:]], 0.25)
     assert rel(b, b1) < 1e-15
     assert rel(c, torch.cat([c2[:1000], tail])) < 1e-15
+
+
+def test_obs_stats_under_capture():
+    """A captured call holds no memory of torch's allocator, and every replay merges the batch as an
+    eager call does, with eager work and allocations in between."""
+    rng = np.random.default_rng(8)
+    x = torch.as_tensor(rng.normal(size=(4096, 37)).astype(np.float32)).cuda()
+    mean, var, inv = (torch.as_tensor(rng.uniform(0.5, 2.0, 37).astype(np.float32)).cuda() for _ in range(3))
+    P.obs_stats_update(x, 1000.0, mean.clone(), var.clone(), inv.clone())   # the library is loaded
+    state, graph = (mean.clone(), var.clone(), inv.clone()), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        before = torch.cuda.memory_stats()["allocation.all.allocated"]
+        P.obs_stats_update(x, 1000.0, *state)
+        after = torch.cuda.memory_stats()["allocation.all.allocated"]
+    assert after == before
+    want = (mean.clone(), var.clone(), inv.clone())
+    for i in range(3):
+        x.copy_(torch.as_tensor(rng.normal(size=(4096, 37)).astype(np.float32)))
+        graph.replay()
+        scribble = [torch.full((4096, 37), float("nan"), device="cuda") for _ in range(4)]
+        P.obs_stats_update(x, 1000.0, *want)
+        torch.cuda.synchronize()
+        for a, b in zip(state, want):
+            assert rel(a, b.cpu()) < 1e-6, i
+        del scribble
