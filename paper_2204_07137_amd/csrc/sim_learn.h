@@ -108,35 +108,40 @@ __device__ __forceinline__ double os_column_sum(const real* __restrict__ x, long
   for (; r < rows; r += OS_GROUPS) p[0] += f((double)x[r * od + c]);
   return ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
 }
-// the row groups' sums of a column, added in group order; every thread of the column gets it
-__device__ __forceinline__ double os_group_sum(double (*red)[OS_COLS], double s, int cl, int grp) {
-  __syncthreads();
-  red[grp][cl] = s;
-  __syncthreads();
-  double t = 0.0;
-  for (int g = 0; g < OS_GROUPS; ++g) t += red[g][cl];
-  return t;
-}
 __global__ __launch_bounds__(OS_COLS * OS_GROUPS) void k_obs_stats(const real* __restrict__ x, long rows, int od,
                                                                     double count, real* __restrict__ mean,
                                                                     real* __restrict__ var, real* __restrict__ inv_std,
                                                                     double eps) {
   __shared__ double red[OS_GROUPS][OS_COLS];
+  __shared__ double bmean[OS_COLS];
   const int cl = threadIdx.x % OS_COLS, grp = threadIdx.x / OS_COLS;
   const int c = blockIdx.x * OS_COLS + cl;
   const bool ok = c < od;
   double s = 0.0, q = 0.0;
   if (ok) s = os_column_sum(x, rows, od, c, grp, [](double v) { return v; });
-  const double bm = os_group_sum(red, s, cl, grp) / (double)rows;
+  red[grp][cl] = s;
+  __syncthreads();
+  if (grp == 0) {
+    double t = 0.0;
+    for (int g = 0; g < OS_GROUPS; ++g) t += red[g][cl];
+    bmean[cl] = t / (double)rows;
+  }
+  __syncthreads();
+  const double bm = bmean[cl];
   if (ok) q = os_column_sum(x, rows, od, c, grp, [bm](double v) { const double d = v - bm; return d * d; });
-  const double m2b = os_group_sum(red, q, cl, grp);
-  if (grp == 0 && ok) os_merge(mean, var, inv_std, c, count, (double)rows, bm, m2b, eps);
+  red[grp][cl] = q;
+  __syncthreads();
+  if (grp == 0 && ok) {
+    double m2b = 0.0;
+    for (int g = 0; g < OS_GROUPS; ++g) m2b += red[g][cl];
+    os_merge(mean, var, inv_std, c, count, (double)rows, bm, m2b, eps);
+  }
 }
 
 // With a workspace: the rows are read once, by as many blocks as there are chunks of them.  The
 // column blocks above leave 2 of 256 CUs working on a 76-column batch: 32768 rows of it take
-// 221 us there and 12.4 us here (10 MB read, two launches), 1024 rows 8.1 and 8.9 us, 2048 rows
-// 13.2 and 9.0 us.  A block of OSP_THREADS threads
+// 221 us there and 12.4 us here (10 MB read, two launches; the rows still in cache).  A block of
+// OSP_THREADS threads
 // takes OSP_UNROLL rows for each of its row groups and w consecutive columns, so that its threads
 // read consecutive words, holds them in registers, and leaves its rows' column sums and sums of
 // squared deviations from its own column means; k_obs_stats_merge joins the chunks:

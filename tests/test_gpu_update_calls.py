@@ -33,6 +33,18 @@ def test_obs_stats_match_oracle(dim, dt, tol):
             assert float((var.double().cpu() - v).abs().max()) < tol * (1.0 + float(v.max()))
 
 
+# the wrapper's own line: wide FP32 batches take the single launch longer
+@pytest.mark.parametrize("dim", [15, 16])
+@pytest.mark.parametrize("rows", [2303, 2304])
+def test_obs_stats_around_the_two_launches(rows, dim):
+    rng = np.random.default_rng(rows + dim)
+    x = torch.as_tensor(rng.normal(size=(rows, dim)).astype(np.float32)).cuda()
+    mean, var, inv = (torch.as_tensor(rng.uniform(0.5, 2.0, dim).astype(np.float32)).cuda() for _ in range(3))
+    n, m, v, s = OL.obs_stats_update(x.cpu(), 500.0, mean.cpu(), var.cpu(), 1e-5)
+    assert P.obs_stats_update(x, 500.0, mean, var, inv) == n
+    assert rel(mean, m) < 1e-6 and rel(var, v) < 1e-6 and rel(inv, s) < 1e-6
+
+
 @pytest.mark.parametrize("h", [1, 7, 8, 9, 17])
 def test_td_lambda_matches_oracle(h):
     rng = np.random.default_rng(h)
