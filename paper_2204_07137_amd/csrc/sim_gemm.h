@@ -841,8 +841,9 @@ __device__ __forceinline__ void adam_element(const LearnAdamT<real>& A, long i, 
   long base = 0;
 #pragma unroll
   for (int t = 1; t < SIM_MAX_TENSORS; ++t) {
+    if (t >= A.n) break;
     base += A.size[t - 1];
-    if (t < A.n && i >= base) p = A.p[t] + (i - base);
+    if (i >= base) p = A.p[t] + (i - base);
   }
   const real m = A.b1 * A.m[i] + (RL(1.0) - A.b1) * gi;
   const real v = A.b2 * A.v[i] + (RL(1.0) - A.b2) * gi * gi;

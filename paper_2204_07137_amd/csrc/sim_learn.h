@@ -25,8 +25,9 @@ __global__ void k_soft_update(SoftUpdateT<real> A, long total) {
   long base = 0;
 #pragma unroll
   for (int k = 1; k < SIM_MAX_TENSORS; ++k) {
+    if (k >= A.n) break;
     base += A.size[k - 1];
-    if (k < A.n && i >= base) {
+    if (i >= base) {
       t = A.t[k] + (i - base);
       o = A.o[k] + (i - base);
     }
