@@ -1,4 +1,4 @@
-// FP32 window kernels: full and muscle layouts, plain per-substep path, MLP weight preparation,
-// window loss and the policy-parameter gradient.
+// FP32 window kernels: full and muscle layouts, plain per-substep path, MLP weight preparation
+// and window loss.
 #define SIM_EMIT_MAIN 1
 #include "sim_unit_f32.h"

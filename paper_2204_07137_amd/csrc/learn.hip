@@ -1,6 +1,5 @@
 // The learning-episode update kernels (actor and critic Adam, TD-lambda, critic fit, target
-// critic), in FP32 and FP64.  A translation unit of its own, with its own instance of the
-// row-contraction GEMMs.
+// critic) and the policy-parameter gradient, which shares their MLP kernels, in FP32 and FP64.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <type_traits>

@@ -1058,8 +1058,8 @@ static int do_window(const WinArgsT<double>& A, int adjoint, int plain, int S, i
   return adjoint ? sim_f64::launch_adjoint(A, plain, S, nv, mtu, lanes, s)
                  : sim_f64::launch_forward(A, plain, S, nv, mtu, lanes, s);
 }
-static int do_theta(const ThetaArgsT<float>& P, void* s) { return sim_f32::launch_theta(P, s); }
-static int do_theta(const ThetaArgsT<double>& P, void* s) { return sim_f64::launch_theta(P, s); }
+static int do_theta(const ThetaArgsT<float>& P, void* s) { return sim_l32::launch_theta(P, s); }
+static int do_theta(const ThetaArgsT<double>& P, void* s) { return sim_l64::launch_theta(P, s); }
 static int group_has_mtu(const int* mtu, int n) {
   for (int i = 0; i < n; ++i)
     if (mtu[i]) return 1;

@@ -371,19 +371,19 @@ struct CriticFitT {
   int launch_forward(const WinArgsT<T>& A, int plain, int substeps, int nv, int mtu, int lanes, void* stream); \
   int launch_adjoint(const WinArgsT<T>& A, int plain, int substeps, int nv, int mtu, int lanes, void* stream); \
   int launch_prep(const WinArgsT<T>& A, void* stream);                                     \
-  int launch_theta(const ThetaArgsT<T>& A, void* stream);                                  \
   int launch_group(const GroupArgsT<T>& G, int adjoint, int mtu, size_t lds_bytes, void* stream); \
   size_t group_lds_bytes(int lanes, int mtu);                                              \
   int prepare_group(size_t lds_bytes);                                                     \
   }
 SIM_DECLARE_LAUNCHERS(sim_f32, float)
 SIM_DECLARE_LAUNCHERS(sim_f64, double)
-// the learning-episode update (learn.hip)
+// the learning-episode update and the policy-parameter gradient (learn.hip)
 #define SIM_DECLARE_LEARN(NS, T)                                                           \
   namespace NS {                                                                           \
   int launch_adam(const LearnAdamT<T>& A, void* stream);                                   \
   int launch_soft_update(const SoftUpdateT<T>& A, void* stream);                           \
   int launch_td_lambda(const T* r, const T* v, const uint8_t* d, int h, int N, T g, T l, T* out, void* s); \
+  int launch_theta(const ThetaArgsT<T>& A, void* stream);                                  \
   int launch_critic_values(const ThetaArgsT<T>& A, T* out, void* stream);                  \
   int launch_obs_stats(const T* x, long rows, int od, double count, T* mean, T* var, T* inv_std, double eps,   \
                        double* ws, void* stream);                                          \

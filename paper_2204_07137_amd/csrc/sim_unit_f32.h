@@ -20,7 +20,4 @@ typedef float real;
 #include "sim_dynamics.h"
 #include "sim_task.h"
 #include "sim_kernels.h"
-#if SIM_EMIT_MAIN
-#include "sim_gemm.h"
-#endif
 }  // namespace sim_f32

@@ -21,7 +21,4 @@ typedef double real;
 #include "sim_dynamics.h"
 #include "sim_task.h"
 #include "sim_kernels.h"
-#if SIM_EMIT_MAIN
-#include "sim_gemm.h"
-#endif
 }  // namespace sim_f64
