@@ -91,7 +91,7 @@ struct SimHandle {
   // policy-gradient scratch: two layer-adjoint buffers, split partials (the hidden
   // activations are the window's own, at off_hid)
   size_t off_th_d0 = 0, off_th_d1 = 0, off_th_part = 0;
-  long th_part_cap = 0;   // values of the split partials
+  long th_part_cap = 0;   // values of the partial gradients
   int n_ckpt = 0;
   int device = -1;
   uint32_t magic = kMagic;
@@ -780,20 +780,21 @@ extern "C" int sim_create(const SimModelDesc* md, const SimOptions* opt, SimHand
   off = align256(off + e * (size_t)opt->horizon * N * h->hid_w);
   if (opt->policy_grad) {
     const size_t rows = N * (size_t)opt->horizon;
-    size_t maxw = 0, maxpart = 0;
+    size_t maxw = 0;
+    long nparams = 0;
     for (int l = 0; l < opt->actor_layers; ++l) {
       maxw = std::max(maxw, (size_t)opt->actor_dims[l + 1]);
-      maxpart = std::max(maxpart, (size_t)opt->actor_dims[l + 1] * (opt->actor_dims[l] + 1));
+      nparams += (long)opt->actor_dims[l + 1] * (opt->actor_dims[l] + 1);
+      if (opt->layer_norm && l + 1 < opt->actor_layers) nparams += 2 * (long)opt->actor_dims[l + 1];
     }
-    // row chunks of at least 512 rows, at most 64 of them
-    const size_t th_splits = std::min<size_t>(64, std::max<size_t>(1, rows / 512));
-    h->th_part_cap = (long)(th_splits * maxpart);
+    // every row chunk's gradient of all layers
+    h->th_part_cap = nparams * sim_wgrad_chunks(opt->actor_dims, opt->actor_layers, (long)rows);
     h->off_th_d0 = off;
     off = align256(off + e * rows * maxw);
     h->off_th_d1 = off;
     off = align256(off + e * rows * maxw);
     h->off_th_part = off;
-    off = align256(off + e * th_splits * maxpart);
+    off = align256(off + e * (size_t)h->th_part_cap);
     if (opt->layer_norm) {
       // the normalised hidden layers of every row and the gain / bias partials
       size_t hw = 0;

@@ -702,7 +702,7 @@ __global__ __launch_bounds__(FIT_WAVES * SIM_WAVE) void k_mlp_fit(FitArgs g) {
 // (16 consecutive columns of four rows), eight row quads requested ahead of their products; the
 // four waves of a block are neighbouring tiles of one chunk and share rows through L1.  Blocks of
 // one chunk run on one XCD (chunk mod 8), so that its rows come into one L2 only.
-#define WG_T 32      // tile side
+#define WG_T SIM_WG_T   // tile side
 #define WG_ST 8      // row quads per stage (the bias sum is written for eight)
 #define WG_XCD 8
 struct WgradArgs {
@@ -1023,21 +1023,18 @@ static int launch_rows(RowsArgs& g, const ThetaArgsT<real>& T, int* n_blocks, in
   return rt == 2 ? launch_rows_as<2, MODE, false>(g, blocks, lds, s) : launch_rows_as<1, MODE, false>(g, blocks, lds, s);
 }
 
-// Row chunks of the weight gradient: enough waves for two on every SIMD, at least 64 rows each,
-// and no more than the partial buffer holds; one chunk writes its gradient straight to T.out.
-#define WG_WAVES (2 * 4 * MR_CUS)
+// Row chunks of the weight gradient: as many as sim_wgrad_chunks has use for and the partial buffer
+// holds; one chunk writes its gradient straight to T.out.
 static void launch_wgrad(WgradArgs& g, const ThetaArgsT<real>& T, hipStream_t s) {
-  auto tiles = [](int no, int ni) { return ((no + WG_T - 1) / WG_T) * ((ni + WG_T - 1) / WG_T); };
-  g.t1 = tiles(T.dims[1], T.dims[0]);
-  g.t2 = g.t1 + (T.nl > 1 ? tiles(T.dims[2], T.dims[1]) : 0);
-  g.t3 = g.t2 + (T.nl > 2 ? tiles(T.dims[3], T.dims[2]) : 0);
+  g.t1 = sim_wgrad_tiles(T.dims[1], T.dims[0]);
+  g.t2 = g.t1 + (T.nl > 1 ? sim_wgrad_tiles(T.dims[2], T.dims[1]) : 0);
+  g.t3 = g.t2 + (T.nl > 2 ? sim_wgrad_tiles(T.dims[3], T.dims[2]) : 0);
   g.ow1 = (int)T.off_w[1]; g.ow2 = (int)T.off_w[2];
   g.ob0 = (int)T.off_b[0]; g.ob1 = (int)T.off_b[1]; g.ob2 = (int)T.off_b[2];
   g.np = mlp_params(T);
-  long n = WG_WAVES / g.t3;
-  const long cap = T.part_cap / g.np, most = T.M / 64;
+  const long cap = T.part_cap / g.np;
+  long n = sim_wgrad_chunks(T.dims, T.nl, T.M);
   n = n < cap ? n : cap;
-  n = n < most ? n : most;
   if (n >= WG_XCD) n = n / WG_XCD * WG_XCD;
   if (n < 1) n = 1;
   g.chunk = (int)(((T.M + n - 1) / n + 3) / 4 * 4);

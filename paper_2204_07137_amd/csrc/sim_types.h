@@ -296,6 +296,20 @@ struct ThetaArgsT {
   long off_g[SIM_MAXL], off_beta[SIM_MAXL];
 };
 
+// Row chunks of k_mlp_wgrad (sim_gemm.h), which takes every layer's weight gradient in one launch of
+// a wave per 32 x 32 tile and chunk: enough waves for two on every SIMD, at least 64 rows each.
+#define SIM_WG_T 32
+#define SIM_WG_WAVES (2 * 4 * 256)
+static inline int sim_wgrad_tiles(int n_out, int n_in) {
+  return ((n_out + SIM_WG_T - 1) / SIM_WG_T) * ((n_in + SIM_WG_T - 1) / SIM_WG_T);
+}
+static inline long sim_wgrad_chunks(const int* dims, int nl, long rows) {
+  int tiles = 0;
+  for (int l = 0; l < nl; ++l) tiles += sim_wgrad_tiles(dims[l + 1], dims[l]);
+  const long n = SIM_WG_WAVES / tiles, most = rows / 64;
+  return n < most ? (n < 1 ? 1 : n) : (most < 1 ? 1 : most);
+}
+
 // Adam over a list of parameter tensors whose gradient and moments are flat, in list order.
 #define SIM_MAX_TENSORS 16
 template <typename T>

@@ -138,3 +138,23 @@ def test_values_of_48_row_tiles(rows, hidden, precision, tol):
     sim, net, _ = _critic(hidden, False, precision)
     x, _ = _inputs(rows)
     assert rel(sim.critic_values(x, _put(net, sim.dtype)), OL.critic_values(net, x, None)) < tol
+
+
+# rows around the chunks of the weight gradient: one chunk, two, eight (whole XCDs), more than a
+# chunk per 64 rows would make, and a ragged last chunk
+@pytest.mark.parametrize("precision,tol", [("fp64", 1e-11), ("fp32", 2e-5)])
+@pytest.mark.parametrize("hidden", [[64, 64], [256, 128]])
+def test_policy_gradient_chunks(hidden, precision, tol):
+    md = wl.model_by_name("cartpole")
+    dims = [5] + hidden + [1]
+    net, critic = wl.mlp_params(dims, 2), wl.mlp_params([5, 64, 1], 3)
+    for N, h in ((127, 1), (128, 1), (256, 2), (733, 5)):
+        print(f"[mlp_rows] theta chunks {hidden} {precision} N={N} h={h}", flush=True)
+        sim = P.Sim(md, N, h, dims, [5, 64, 1], policy_grad=True, precision=precision)
+        fw = sim.forward(wl.initial_states(md, N, 1), net, critic)
+        ad = sim.adjoint(fw, want_theta=True)
+        layers = [(torch.as_tensor(W).requires_grad_(), torch.as_tensor(b).requires_grad_()) for W, b in net]
+        a = torch.tanh(mlp_forward(layers, fw["obs"][:h].double().cpu().reshape(-1, 5), None))
+        grads = torch.autograd.grad(a, [t for pair in layers for t in pair], ad["dL_da"].double().cpu().reshape(-1, 1))
+        assert rel(ad["dL_dtheta_flat"], torch.cat([g.reshape(-1) for g in grads])) < tol
+        sim.close()
