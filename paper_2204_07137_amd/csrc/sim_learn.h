@@ -293,21 +293,30 @@ int launch_critic_values(const ThetaArgsT<real>& T, real* out, void* stream) {
 
 template <int RT, bool LN>
 static int launch_fit_as(const FitArgs& g, int tiles, size_t lds, hipStream_t s) {
+  if (allow_lds(&k_mlp_fit<RT, LN>, lds)) return -1;
   hipLaunchKernelGGL((k_mlp_fit<RT, LN>), dim3(tiles), dim3(FIT_WAVES * SIM_WAVE), lds, s, g);
   return 0;
 }
 
 // Whether a minibatch of M rows runs as k_mlp_fit with rt x 16 rows a block: the tile's layers
-// within 52 KB of LDS (three blocks a CU), the tiles' gradients within the scratch, and at most
-// FIT_PARAMS_PER_ROW gradient values written per row (beyond that the gradients are more traffic
-// than the layer inputs and adjoints that k_mlp_rows and k_mlp_wgrad exchange).
+// within a CU's LDS, the tiles' gradients within the scratch, and at most FIT_PARAMS_PER_ROW
+// gradient values written per row (beyond that the gradients are more traffic than the layer
+// inputs and adjoints that k_mlp_rows and k_mlp_wgrad exchange).  32 rows a block once they give
+// every CU a block, if two such blocks fit a CU; else 16 rows if three fit; else whatever fits:
+// a block alone on its CU still beats the three launches and the layers (76-256-128-1, 8192 rows:
+// 59 us fused with 32 rows in 63 KB, 105 and 168 us; FP64 280-64-64-1, 256 rows: 29 us with 16 rows in
+// 57 KB, 43 us in three launches), but 12288 rows of a normalised 76-128-128-1 take 85 us as 32-row
+// blocks of 86 KB and 68 us as 16-row blocks of 45 KB.
 #define FIT_PARAMS_PER_ROW 2048
 static bool fit_plan(const CriticFitT<real>& F, int M, FitArgs& g, int& rt, size_t& lds) {
   const ThetaArgsT<real>& T = F.G;
   const long np = mlp_params(T);
   auto ld = [&](int l) { return l < T.nl ? mlp_pad16(T.dims[l]) + 4 : 0; };
   g.ld0 = ld(0); g.ld1 = ld(1); g.ld2 = ld(2);
-  for (rt = M >= 32 * MR_CUS ? 2 : 1; rt >= 1; --rt) {
+  const struct { int rt; size_t lds; } form[] = {{2, 80 << 10}, {1, 160 * 1024 / 3}, {2, 160 << 10}, {1, 160 << 10}};
+  for (const auto& f : form) {
+    rt = f.rt;
+    if (rt == 2 && M < 32 * MR_CUS) continue;
     const int R = 16 * rt, copies = T.ln ? 2 : 1;
     g.p1 = R * g.ld0;
     g.e1 = g.p1 + R * g.ld1;
@@ -315,7 +324,9 @@ static bool fit_plan(const CriticFitT<real>& F, int M, FitArgs& g, int& rt, size
     g.e2 = g.p2 + R * g.ld2;
     g.pd = g.p2 + copies * R * g.ld2;
     lds = (size_t)(g.pd + R * 20) * sizeof(real);
-    if (lds <= 53248 && np <= (long)FIT_PARAMS_PER_ROW * R && (long)((M + R - 1) / R) * np <= F.scratch_cap) return true;
+    // with the kernel's own arrays: statistics, row sums, the normalisation's column sums
+    const size_t all = lds + ((MR_MAXHIDL * 2 + 3) * R + (T.ln ? 1024 : 1)) * sizeof(real);
+    if (all <= f.lds && np <= (long)FIT_PARAMS_PER_ROW * R && (long)((M + R - 1) / R) * np <= F.scratch_cap) return true;
   }
   return false;
 }
