@@ -16,7 +16,7 @@ LIB_PHASE = os.path.join(HERE, "libshacsim_phase.so")
 SOURCES = [os.path.join(HERE, "csrc", f) for f in ("kernels_f32_group_fwd.hip", "kernels_f32_group_adj.hip", "kernels_f32.hip",
                                                   "kernels_f32_compact.hip", "kernels_f64.hip", "kernels_f64_group_fwd.hip",
                                                   "kernels_f64_group_adj.hip", "shacsim_abi.hip", "learn.hip")]
-HEADERS = [os.path.join(HERE, "csrc", f) for f in ("sim_types.h", "sim_math.h", "sim_dynamics.h", "sim_task.h", "sim_gemm.h", "sim_learn.h",
+HEADERS = [os.path.join(HERE, "csrc", f) for f in ("sim_types.h", "sim_math.h", "sim_dynamics.h", "sim_task.h", "sim_gemm.h", "sim_layers.h", "sim_learn.h",
                                                  "sim_kernels.h", "sim_unit_f32.h", "sim_unit_f64.h")] + [
     os.path.join(ROOT, "include", "shacsim.h")]
 

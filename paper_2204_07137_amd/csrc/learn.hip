@@ -9,6 +9,7 @@ namespace sim_l32 {
 typedef float real;
 #include "sim_math.h"
 #include "sim_gemm.h"
+#include "sim_layers.h"
 #include "sim_learn.h"
 }  // namespace sim_l32
 
@@ -16,5 +17,6 @@ namespace sim_l64 {
 typedef double real;
 #include "sim_math.h"
 #include "sim_gemm.h"
+#include "sim_layers.h"
 #include "sim_learn.h"
 }  // namespace sim_l64

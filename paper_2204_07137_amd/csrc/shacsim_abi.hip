@@ -91,6 +91,7 @@ struct SimHandle {
   // policy-gradient scratch: two layer-adjoint buffers, split partials (the hidden
   // activations are the window's own, at off_hid)
   size_t off_th_d0 = 0, off_th_d1 = 0, off_th_part = 0;
+  int th_splits = 0;      // row chunks of a layer by itself
   long th_part_cap = 0;   // values of the partial gradients
   int n_ckpt = 0;
   int device = -1;
@@ -780,15 +781,19 @@ extern "C" int sim_create(const SimModelDesc* md, const SimOptions* opt, SimHand
   off = align256(off + e * (size_t)opt->horizon * N * h->hid_w);
   if (opt->policy_grad) {
     const size_t rows = N * (size_t)opt->horizon;
-    size_t maxw = 0;
+    size_t maxw = 0, maxpart = 0;
     long nparams = 0;
     for (int l = 0; l < opt->actor_layers; ++l) {
+      maxpart = std::max(maxpart, (size_t)opt->actor_dims[l + 1] * (opt->actor_dims[l] + 1));
       maxw = std::max(maxw, (size_t)opt->actor_dims[l + 1]);
       nparams += (long)opt->actor_dims[l + 1] * (opt->actor_dims[l] + 1);
       if (opt->layer_norm && l + 1 < opt->actor_layers) nparams += 2 * (long)opt->actor_dims[l + 1];
     }
-    // every row chunk's gradient of all layers
-    h->th_part_cap = nparams * sim_wgrad_chunks(opt->actor_dims, opt->actor_layers, (long)rows);
+    // every row chunk's gradient of all layers, or of one layer after the other (then chunks of at
+    // least 512 rows, at most 64 of them)
+    h->th_splits = (int)std::min<size_t>(64, std::max<size_t>(1, rows / 512));
+    h->th_part_cap = std::max(nparams * sim_wgrad_chunks(opt->actor_dims, opt->actor_layers, (long)rows),
+                              (long)(h->th_splits * maxpart));
     h->off_th_d0 = off;
     off = align256(off + e * rows * maxw);
     h->off_th_d1 = off;
@@ -1013,6 +1018,7 @@ static void build_theta_args(SimHandle* h, const SimAdjointIO* io, ThetaArgsT<T>
   P.d1 = reinterpret_cast<T*>(ws + h->off_th_d1);
   P.part = reinterpret_cast<T*>(ws + h->off_th_part);
   P.part_cap = h->th_part_cap;
+  P.splits = h->th_splits;
   P.out = static_cast<T*>(io->dL_dtheta);
   // the gradient is taken at the activations the window itself computed (stored by the
   // forward), rows (t, env) as the observations' (handles with BF16 MLPs have no dL/dtheta,
@@ -1025,7 +1031,6 @@ static void build_theta_args(SimHandle* h, const SimAdjointIO* io, ThetaArgsT<T>
       P.ldH[l] = h->hid_w;
       off_l += o.actor_dims[l];
     }
-    P.hidden_given = 1;
     if (o.layer_norm && o.actor_layers > 1) {
       P.ln = 1;
       P.st = hid + off_l;
@@ -1815,6 +1820,7 @@ static void critic_theta_args(const SimHandle* h, const CriticWs& w, char* ws, c
   P.d1 = reinterpret_cast<T*>(ws + w.d1);
   P.part = reinterpret_cast<T*>(ws + w.part);
   P.part_cap = (long)w.part_n;
+  P.splits = CRITIC_SPLITS;
   P.out = reinterpret_cast<T*>(ws + w.grad);
 }
 

@@ -5,7 +5,8 @@
 // and env; the action adjoint is carried back through the squash and every ELU layer, and
 // the weight gradient of a layer is the contraction of its output adjoint with its input
 // over all rows.  The critic's calls (values, minibatch fit) use the same kernels and
-// compute their hidden layers themselves.
+// compute their hidden layers themselves.  Networks and row counts for which these tiles of rows
+// are the slower form go layer by layer (sim_layers.h).
 //
 // Kernels, each one launch whatever the depth of the network:
 //   k_mlp_fit     a minibatch's 16 or 32 rows per block through every layer, back, and into the
@@ -1058,25 +1059,4 @@ static void reduce_args(ReduceArgs& Q, const ThetaArgsT<real>& T, const real* pa
   Q.n1 = apart ? 2 * T.dims[1] : 0;
   Q.og2 = apart && T.nl > 2 ? T.off_g[1] : 0;
   Q.n2 = apart && T.nl > 2 ? 2 * T.dims[2] : 0;
-}
-
-int launch_theta(const ThetaArgsT<real>& T, void* stream) {
-  hipStream_t s = (hipStream_t)stream;
-  if (T.nl > 1 && !T.hidden_given) return -1;   // the gradient is taken at the window's own activations
-  RowsArgs R = {};
-  int blocks = 0;
-  if (T.nl > 1 && launch_rows<ROWS_THETA>(R, T, &blocks, nullptr, s)) return -1;
-  if (T.noise && T.out_log_std)
-    hipLaunchKernelGGL(k_log_std_grad, dim3(T.dims[T.nl]), dim3(256), 0, s, T.da, T.act, T.noise, T.log_std, (long)T.M,
-                       T.dims[T.nl], T.mtu, T.out_log_std);
-  WgradArgs W = {};
-  W.N = mlp_net(T);
-  launch_wgrad(W, T, s);
-  if (W.splits > 1 || T.ln) {
-    ReduceArgs Q = {};
-    reduce_args(Q, T, W.part, W.splits, blocks, true);
-    Q.out = T.out;
-    hipLaunchKernelGGL(k_mlp_reduce, dim3((unsigned)((Q.np + SIM_WAVE - 1) / SIM_WAVE)), dim3(RD_WAVES * SIM_WAVE), 0, s, Q);
-  }
-  return hipGetLastError() == hipSuccess ? 0 : -1;
 }

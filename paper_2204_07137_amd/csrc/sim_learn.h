@@ -2,10 +2,10 @@
 // step of the policy, TD-lambda value estimates of the window's states from the target
 // critic, the critic's mean-squared-error fit over shuffled minibatches with Adam, and the
 // smooth update of the target critic.  The contractions run on the matrix cores through the
-// row-contraction GEMMs of the policy-parameter gradient (sim_gemm.h).
+// kernels of the policy-parameter gradient (sim_gemm.h, sim_layers.h).
 //
-// Included inside a namespace with `real` defined as float or double, after sim_math.h and
-// sim_gemm.h.
+// Included inside a namespace with `real` defined as float or double, after sim_math.h,
+// sim_gemm.h and sim_layers.h.
 
 // one Adam step (adam_element) over every tensor of a list in one launch
 __global__ void k_adam_multi(LearnAdamT<real> A, long total) {
@@ -67,6 +67,21 @@ __global__ void k_td_lambda(const real* __restrict__ r, const real* __restrict__
       out[(size_t)(t1 - u) * N + e] = G;
     }
   }
+}
+
+// minibatch rows: x[b] = obs[perm[b]], y[b] = targets[perm[b]]
+// (normalised with the running statistics when given: x = (o - mean) * inv_std)
+__global__ void k_gather_rows(const real* __restrict__ obs, const real* __restrict__ tgt, const int* __restrict__ perm,
+                              int B, int od, const real* __restrict__ mean, const real* __restrict__ inv_std,
+                              real* __restrict__ x, real* __restrict__ y) {
+  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= (long)B * od) return;
+  const int b = (int)(i / od), c = (int)(i % od);
+  const int r = perm[b];
+  real v = obs[(long)r * od + c];
+  if (mean) v = (v - mean[c]) * inv_std[c];
+  x[i] = v;
+  if (c == 0) y[b] = tgt[r];
 }
 
 // Running observation statistics (Sec. 3.3): merges a batch of rows into the count, mean
@@ -243,6 +258,30 @@ __global__ __launch_bounds__(OSM_COLS * OSM_GROUPS) void k_obs_stats_merge(const
   if (grp == 0 && ok) os_merge(mean, var, inv_std, c, count, (double)rows, bm, m2b, eps);
 }
 
+// output adjoint of the mean squared error (1/B) sum (V - y)^2
+__global__ void k_mse_seed(const real* __restrict__ V, const real* __restrict__ y, int B, real* __restrict__ d) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < B) d[i] = RL(2.0) / (real)B * (V[i] - y[i]);
+}
+
+// the minibatch's mean squared error before the step, by a fixed-order tree (one block)
+__global__ __launch_bounds__(256) void k_mse_loss(const real* __restrict__ V, const real* __restrict__ y, int B,
+                                                  real* __restrict__ out) {
+  __shared__ real part[256];
+  real s = RL(0.0);
+  for (int i = threadIdx.x; i < B; i += 256) {
+    const real d = V[i] - y[i];
+    s += d * d;
+  }
+  part[threadIdx.x] = s;
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if (threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) *out = part[0] / (real)B;
+}
+
 static void launch_adam_multi(const LearnAdamT<real>& A, hipStream_t s) {
   long total = 0;
   for (int i = 0; i < A.n; ++i) total += A.size[i];
@@ -285,9 +324,15 @@ int launch_obs_stats(const real* x, long rows, int od, double count, real* mean,
 }
 
 int launch_critic_values(const ThetaArgsT<real>& T, real* out, void* stream) {
-  RowsArgs R = {};
-  R.V = out;
-  if (launch_rows<ROWS_VALUES>(R, T, nullptr, nullptr, (hipStream_t)stream)) return -1;
+  hipStream_t s = (hipStream_t)stream;
+  if (layered(T, ROWS_VALUES)) {
+    theta_hidden(T, s);
+    theta_output(T, out, s);
+  } else {
+    RowsArgs R = {};
+    R.V = out;
+    if (launch_rows<ROWS_VALUES>(R, T, nullptr, nullptr, s)) return -1;
+  }
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -331,9 +376,28 @@ static bool fit_plan(const CriticFitT<real>& F, int M, FitArgs& g, int& rt, size
   return false;
 }
 
+// One minibatch layer by layer: gather, forward, loss adjoint, layer gradients, Adam step.
+static void fit_layers(const CriticFitT<real>& F, const ThetaArgsT<real>& G, const int* perm, const LearnAdamT<real>& A,
+                       real* loss_out, hipStream_t s) {
+  const int B = G.M;
+  const long nx = (long)B * G.dims[0];
+  hipLaunchKernelGGL(k_gather_rows, dim3((unsigned)((nx + 255) / 256)), dim3(256), 0, s, F.obs, F.targets, perm, B,
+                     G.dims[0], F.obs_mean, F.obs_inv_std, F.x, F.y);
+  ThetaArgsT<real> T = G;
+  T.x0 = F.x;
+  T.x_shift = T.x_scale = nullptr;
+  theta_hidden(T, s);
+  theta_output(T, F.vbuf, s);
+  if (loss_out) hipLaunchKernelGGL(k_mse_loss, dim3(1), dim3(256), 0, s, F.vbuf, F.y, B, loss_out);
+  hipLaunchKernelGGL(k_mse_seed, dim3((unsigned)((B + 255) / 256)), dim3(256), 0, s, F.vbuf, F.y, B, T.d0);
+  theta_backward(T, s);
+  launch_adam_multi(A, s);
+}
+
 // n_iter passes over the rows in the order of perm[it], n_mb minibatches each.  A minibatch is
-// two launches: the tiles' gradients, and their sum with the Adam step; larger networks take
-// three (the rows pass, every layer's weight gradient, the sum with the Adam step).
+// two launches where its tiles fit (fit_plan): the tiles' gradients, and their sum with the Adam
+// step.  Others take three, the rows pass, every layer's weight gradient, and the sum with the
+// Adam step, or go layer by layer (layered).
 int launch_critic_fit(const CriticFitT<real>& F, void* stream) {
   hipStream_t s = (hipStream_t)stream;
   ThetaArgsT<real> T = F.G;
@@ -358,7 +422,7 @@ int launch_critic_fit(const CriticFitT<real>& F, void* stream) {
       A.size[A.n++] = T.dims[l + 1];
     }
   }
-  A.m = F.m; A.v = F.v;
+  A.g = T.out; A.m = F.m; A.v = F.v;
   A.lr = F.lr; A.b1 = F.b1; A.b2 = F.b2; A.eps = F.eps;
   int step = F.adam_step;
   for (int it = 0; it < F.n_iter; ++it) {
@@ -367,6 +431,10 @@ int launch_critic_fit(const CriticFitT<real>& F, void* stream) {
       if (r1 <= r0) continue;
       T.M = r1 - r0;
       const int* perm = F.perm + (long)it * F.rows + r0;
+      real* loss_out = F.loss_out ? F.loss_out + it * F.n_mb + mb : nullptr;
+      ++step;
+      A.bc1 = RL(1.0) - (real)pow((double)F.b1, (double)step);
+      A.bc2 = RL(1.0) - (real)pow((double)F.b2, (double)step);
       FitArgs g = {};
       int rt;
       size_t lds;
@@ -386,6 +454,9 @@ int launch_critic_fit(const CriticFitT<real>& F, void* stream) {
         if (bad) return -1;
         reduce_args(Q, T, F.scratch, tiles, 0, false);
         Q.n_loss = tiles;
+      } else if (layered(T, ROWS_FIT)) {
+        fit_layers(F, T, perm, A, loss_out, s);
+        continue;
       } else {
         RowsArgs R = {};
         R.perm = perm;
@@ -403,10 +474,7 @@ int launch_critic_fit(const CriticFitT<real>& F, void* stream) {
         reduce_args(Q, T, W.part, W.splits, blocks, true);
       }
       Q.rows = T.M;
-      Q.loss_out = F.loss_out ? F.loss_out + it * F.n_mb + mb : nullptr;
-      ++step;
-      A.bc1 = RL(1.0) - (real)pow((double)F.b1, (double)step);
-      A.bc2 = RL(1.0) - (real)pow((double)F.b2, (double)step);
+      Q.loss_out = loss_out;
       Q.A = A;
       hipLaunchKernelGGL(k_mlp_reduce, dim3((unsigned)((Q.np + SIM_WAVE - 1) / SIM_WAVE) + 1), dim3(RD_WAVES * SIM_WAVE), 0, s, Q);
     }

@@ -272,18 +272,17 @@ struct ThetaArgsT {
   T* out_log_std;             // [na] dL/dlog_std (with noise), or null
   T* H[SIM_MAXL];             // H[l] (l >= 1): [M][dims[l]] hidden activations
   long ldH[SIM_MAXL];         // row stride of H[l] (0: dims[l])
-  int hidden_given;           // H holds the activations already (the window's own): no recompute
-  T* d0;                      // [M][dims[1]] adjoint of the first hidden layer's pre-activations
-  T* d1;                      // [M][dims[2]] of the second's
+  T* d0;                      // [M][widest layer] layer adjoints: two buffers that take turns, or
+  T* d1;                      // the first and the second hidden layer's
   T* part;                    // partial weight gradients, part_cap values
   long part_cap;
+  int splits;                 // row chunks of one layer's partial gradients that part_cap allows
   T* out;                     // flat dL/dtheta: W_0, b_0, W_1, b_1, ...
   long off_w[SIM_MAXL], off_b[SIM_MAXL];
   // layer normalisation of the hidden layers: H[l] then holds the ELU outputs, st + r * ldst
-  // the per-row mean and inverse deviation of each hidden layer (the window's, or computed by
-  // the hidden-layer pass with ln_eps), Y[l] ([M][dims[l]], scratch) the normalised layer
-  // inputs, lnpart (lnpart_cap values) the per-block partial sums of the gain and bias
-  // gradients (flat at off_g / off_beta)
+  // the per-row mean and inverse deviation of each hidden layer (the window's, or a critic's with
+  // ln_eps), Y[l] ([M][dims[l]], scratch) the normalised layer inputs, lnpart (lnpart_cap
+  // values) the per-block partial sums of the gain and bias gradients (flat at off_g / off_beta)
   int ln;
   T ln_eps;
   const T* lng[SIM_MAXL];
@@ -364,8 +363,8 @@ struct CriticFitT {
   const int* perm;      // [n_iter][rows]
   int rows, n_iter, n_mb;
   T* x;                 // [rows][obs_dim] gathered minibatch
-  T* y;                 // [rows] squared-error sums of the row tiles
-  T* vbuf;              // [rows] output adjoints
+  T* y;                 // [rows] its targets, or squared-error sums of the row tiles
+  T* vbuf;              // [rows] critic outputs, or output adjoints
   T* scratch;           // the workspace from vbuf on, scratch_cap values: the row tiles' gradients
   long scratch_cap;
   T* W[SIM_MAXL];       // critic weights, updated in place
