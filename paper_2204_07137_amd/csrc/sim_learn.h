@@ -11,7 +11,7 @@
 __global__ void k_adam_multi(LearnAdamT<real> A, long total) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= total) return;
-  adam_element(A, i, A.g[i]);
+  adam_element<true>(A, i, A.g[i]);
 }
 
 // target <- alpha target + (1 - alpha) online over every tensor of a list in one launch (a
