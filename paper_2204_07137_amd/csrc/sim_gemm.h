@@ -1008,11 +1008,13 @@ static int launch_rows(RowsArgs& g, const ThetaArgsT<real>& T, int* n_blocks, in
   g.lnpart = T.lnpart;
   const size_t row_bytes = 2 * (size_t)g.ld * sizeof(real);
   int rt = (T.M >= 32 * MR_CUS && 32 * row_bytes <= 65536) ? 2 : 1;
-  // values of more 32-row tiles than fit the CUs at once (four each) but no more 48-row tiles than
-  // do (three each): one round of blocks instead of a second for a few
-  if (MODE == ROWS_VALUES && rt == 2 && (T.M + 31) / 32 > 4 * MR_CUS && (T.M + 47) / 48 <= 3 * MR_CUS &&
-      48 * row_bytes <= 53248)
-    rt = 3;
+  // A CU holds four 32-row tiles of values or three of 48 rows (FP64: two of either), and a round of
+  // tiles takes about as long as it has rows: 48 rows where their rounds hold no more rows.  A
+  // 76-128-128-1 critic in FP32: 33792 rows 44 us with 32 rows a block (two rounds) and 33 us with 48
+  // (one), 69632 rows 1.10 and 73728 rows 1.14 times faster, 40960 rows 5 % slower (two rounds of either).
+  constexpr int b2 = sizeof(real) == 8 ? 2 : 4, b3 = sizeof(real) == 8 ? 2 : 3;
+  auto round_rows = [&](int r, int b) { return (T.M + 16L * r * b * MR_CUS - 1) / (16L * r * b * MR_CUS) * r * b; };
+  if (MODE == ROWS_VALUES && rt == 2 && 48 * row_bytes <= 53248 && round_rows(3, b3) <= round_rows(2, b2)) rt = 3;
   const int tiles = (T.M + 16 * rt - 1) / (16 * rt);
   int blocks = tiles;
   if (T.ln && MODE != ROWS_VALUES && g.lnw > 0 && blocks > T.lnpart_cap / g.lnw) blocks = (int)(T.lnpart_cap / g.lnw);

@@ -158,3 +158,18 @@ def test_policy_gradient_chunks(hidden, precision, tol):
         grads = torch.autograd.grad(a, [t for pair in layers for t in pair], ad["dL_da"].double().cpu().reshape(-1, 1))
         assert rel(ad["dL_dtheta_flat"], torch.cat([g.reshape(-1) for g in grads])) < tol
         sim.close()
+
+
+# around the row counts at which a round of 48-row tiles begins to save a round of 32-row tiles, or no
+# longer does (FP32: two against three rounds above 65536; FP64: one against two above 16384)
+@pytest.mark.parametrize("precision,tol,rows", [("fp32", 1e-5, (36865, 65537, 73728, 73729)),
+                                                ("fp64", 1e-12, (16385, 24576, 24577))])
+@pytest.mark.parametrize("layer_norm", [False, True])
+def test_values_around_the_rounds_of_tiles(layer_norm, precision, tol, rows):
+    sim, net, ln = _critic([64, 64], layer_norm, precision)
+    x, _ = _inputs(max(rows))
+    want = OL.critic_values(net, x, ln)
+    for n in rows:
+        print(f"[mlp_rows] values of {n} rows ln={layer_norm} {precision}", flush=True)
+        got = sim.critic_values(x[:n], _put(net, sim.dtype), critic_ln=_put(ln, sim.dtype) if ln else None)
+        assert rel(got, want[:n]) < tol
