@@ -278,7 +278,7 @@ static void convert_model(const DevModelT<double>& s, DevModelT<T>& d) {
   d.chol_thr = (T)s.chol_thr;
   for (int j = 0; j < SIM_MAXJ; ++j) {
     d.parent[j] = s.parent[j]; d.jtype[j] = s.jtype[j]; d.qadr[j] = s.qadr[j]; d.vadr[j] = s.vadr[j];
-    d.depth[j] = s.depth[j]; d.first_child[j] = s.first_child[j]; d.next_sib[j] = s.next_sib[j];
+    d.depth[j] = s.depth[j];
     d.act_of_joint[j] = s.act_of_joint[j]; d.limited[j] = s.limited[j];
     d.mass[j] = (T)s.mass[j]; d.lower[j] = (T)s.lower[j]; d.upper[j] = (T)s.upper[j]; d.gear[j] = (T)s.gear[j];
     for (int k = 0; k < 3; ++k) {
@@ -329,7 +329,7 @@ static int build_model(const SimModelDesc* md, DevModelT<double>& m) {
       !md->limited || !md->lower || !md->upper || !md->armature)
     return fail(SIM_E_ARG, "sim_create: null model array");
   for (int j = 0; j < SIM_MAXJ; ++j) {
-    m.first_child[j] = -1; m.next_sib[j] = -1; m.act_of_joint[j] = -1; m.parent[j] = -1; m.depth[j] = -1;
+    m.act_of_joint[j] = -1; m.parent[j] = -1; m.depth[j] = -1;
   }
   int nq = 0, nv = 0, maxd = 0;
   for (int j = 0; j < J; ++j) {
@@ -364,13 +364,6 @@ static int build_model(const SimModelDesc* md, DevModelT<double>& m) {
     m.upper[j] = md->upper[j];
   }
   if (nv > SIM_MAXV || nq > SIM_MAXQ) return fail(SIM_E_MODEL, "more than 32 velocity DOFs");
-  for (int j = J - 1; j >= 1; --j) {
-    int p = m.parent[j];
-    if (p >= 0) {
-      m.next_sib[j] = m.first_child[p];
-      m.first_child[p] = j;
-    }
-  }
   if (md->n_act < 0 || md->n_act > SIM_MAXA) return fail(SIM_E_MODEL, "n_act out of range [0, 32]");
   if (md->n_act > 0 && (!md->act_joint || !md->gear)) return fail(SIM_E_ARG, "null actuator arrays");
   for (int i = 0; i < md->n_act; ++i) {

@@ -93,7 +93,10 @@ struct EnvLDST {
   real qb[CV + 1], qdb[CV], abar[MAXA];
   real lam[CV], dPq[CV], dPqd[CV];
   // topology copies for arbitrary-index lookups
-  int t_next_sib[CJ], t_type[CJ], t_va[CJ], t_parent[CJ], t_qa[CJ];
+  // unused: the tables that follow lie better across the LDS banks behind it (the humanoid window of
+  // 1024 environments takes 34.25 ms, 34.65 without)
+  int t_pad[CJ];
+  int t_type[CJ], t_va[CJ], t_parent[CJ], t_qa[CJ];
   real arm[CV];
   real j_off[CJ][3], j_ax[CJ][3], j_com[CJ][3], j_I6[CJ][6];
   int pairs[CPAIR];
@@ -151,7 +154,7 @@ __device__ __forceinline__ void load_regs(const DevModel* __restrict__ m, L& E, 
   int c = ln < m->nc ? ln : 0;
   cr.body = m->cbody[c]; cr.pos = ld3(&m->cpos[3 * c]); cr.rad = m->crad[c];
   for (int f = ln; f < L::kJ; f += LN) {
-    E.t_next_sib[f] = m->next_sib[f]; E.t_type[f] = m->jtype[f];
+    E.t_type[f] = m->jtype[f];
     E.t_va[f] = m->vadr[f]; E.t_parent[f] = m->parent[f]; E.t_qa[f] = m->qadr[f];
   }
   for (int f = ln; f < L::kV; f += LN) E.arm[f] = m->armature[f];
@@ -506,8 +509,8 @@ __device__ __forceinline__ void lds_add6(real* dst, sv w) {
 // left is bound by the instructions of one wavefront.  The additions as LDS atomics, in the same
 // order (an instruction's additions to one address are performed in lane order, so both forms
 // give the same sums bit for bit), were bound by the LDS, which performs about 1.5 of the 64
-// lanes' additions per cycle: with four 152-muscle environments on a CU they took 19 k cycles of
-// the forward substep's 75 k and 68 k of its adjoint's 206 k; the schedule takes 13 k and 23 k.
+// lanes' additions per cycle: with four 152-muscle environments on a CU they took 16.9 k cycles of
+// the forward substep's 74 k and 63.9 k of its adjoint's 204 k; the schedule takes 13 k and 23 k.
 // Models beyond the schedule's capacity (more runs per unit or pass, or pairs, than it has room
 // for) keep the atomics.
 template <class L>

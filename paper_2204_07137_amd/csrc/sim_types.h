@@ -126,7 +126,7 @@ struct DevModelT {
   T tau_act, fl_w, vmax;     // activation time constant, force-length width, max fibre speed (l_opt/s)
   T term_h;
   int parent[SIM_MAXJ], jtype[SIM_MAXJ], qadr[SIM_MAXJ], vadr[SIM_MAXJ], depth[SIM_MAXJ];
-  int first_child[SIM_MAXJ], next_sib[SIM_MAXJ], act_of_joint[SIM_MAXJ], limited[SIM_MAXJ];
+  int act_of_joint[SIM_MAXJ], limited[SIM_MAXJ];
   T offset[SIM_MAXJ * 3], axis[SIM_MAXJ * 3], mass[SIM_MAXJ], com[SIM_MAXJ * 3];
   T inertia[SIM_MAXJ * 6];   // xx yy zz xy xz yz about the COM, frame axes
   T lower[SIM_MAXJ], upper[SIM_MAXJ], gear[SIM_MAXJ];
