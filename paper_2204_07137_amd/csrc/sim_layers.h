@@ -372,18 +372,34 @@ static void theta_backward(const ThetaArgsT<real>& T, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------- the choice
+// Loads a wave of a row tile waits for one after the other in a forward pass: 32 values of k for two
+// column tiles (one below 128 columns) at a time
+static int row_chain(const ThetaArgsT<real>& T) {
+  int c = 0;
+  for (int l = 0; l + 1 < T.nl; ++l) {
+    const int cols = MR_WAVES * 16 * (T.dims[l + 1] >= 128 ? 2 : 1);
+    c += (T.dims[l + 1] + cols - 1) / cols * ((T.dims[l] + 31) / 32);
+  }
+  return c;
+}
+
 // Whether the rows of a call go layer by layer, or as row tiles (sim_gemm.h).  A block of row tiles
 // streams all weights: with few rows a wide network is a chain of loads on a few CUs, and with many
 // rows its weights are read once per tile.  Layer by layer a call is three to fifteen launches, whose
-// contractions take any width well.  So the lines lie by the network's parameters np, the rows M
-// and, with layer normalisation, whose passes over the hidden layers cost the tiles most, the sum hs
-// of the hidden widths; FP64 streams twice the bytes.  Measured, as time layer by layer over time in
-// tiles (above one: tiles), at 12 row counts of 12 networks for each line; the muscle critic is
-// 280-400-200-1 (193 k parameters), the other inputs 76:
-//   values  FP32 muscle critic 0.91 at 64 to 1024 rows, 0.95 at 2048, 1.09 at 3072, 1.8 at 32768;
-//           400-200 (111 k) 1.12 from 16 rows on, 0.95 at one.  FP64 0.87, 0.93, 1.37 and 1.27; 1.04, 0.90.
-//           Normalised: FP32 muscle critic 1.13, 512-512 (407 k) 0.90 at 256 and 1.04 at 1536; FP64 muscle
-//           critic 0.90 at 512, 1.02 at 1536.
+// contractions take any width well.  So the lines lie by the rows M and, for values, by the chain c
+// of loads, with weights that are not in L2 (a program asks for values once per episode, behind a
+// window); for fits and the policy gradient by the network's parameters np and, with layer
+// normalisation, whose passes over the hidden layers cost the tiles most, the sum hs of the hidden
+// widths; FP64 streams twice the bytes.  Measured, as time layer by layer over time in tiles (above
+// one: tiles), at 12 to 15 row counts of 12 networks for each line; the muscle critic is 280-400-200-1
+// (193 k parameters, c 62), the other inputs 76 or named:
+//   values  FP32 256-128 (c 14) 1.35 to 2.1 from 64 rows on; 280-256-128 (26) 1.07 to 2.0, 0.78 at one row;
+//           300-200 (29) 0.80 to 0.94 to 4096 rows, 1.24 at 5000; 400-200 (38) 0.70 to 0.90 and 1.06; muscle
+//           critic 0.58 to 0.80, 0.94 at 6144, 1.36 at 8000.  Normalised 280-512 (36) 1.12 from 64 rows on, 0.90
+//           at one; muscle critic 1.01 to 2.2, 0.83 at one; 37-512-512 (72) 0.76 to 0.91 to 2048, 1.02 at 2560.  FP64
+//           280-256-128 1.27, 5-400-200 (30) 0.91 to 0.98 to 2048 rows and 1.14 at 2560; muscle critic 0.77 to
+//           0.82, 1.12 at 2560, 0.84 at 4500, 1.17 at 8000.  Normalised FP64 400-200 0.90 to 0.95 to 1024 and 1.02
+//           at 1536, muscle critic 0.80 to 0.88 to 2048 and 1.16 at 2560.
 //   fit     FP32 to 111 k parameters 0.98 to 2.1; muscle critic 0.87 at 64, 1.05 at 512, 1.1 to 1.3 from 1024
 //           on; 512-512 0.62 to 0.93.  FP64 53 k 1.13 to 1.57 to 4096 rows, 0.99 at 6144, 0.73 at 32768; 76 k
 //           0.88 at 64, 1.07 to 1.16 from 512 to 4096; 83 k 0.80 to 1.05 to 2048, 1.08 to 1.20 at 3072 and
@@ -399,8 +415,10 @@ static bool layered(const ThetaArgsT<real>& T, int mode) {
   double hs = 0;
   for (int l = 1; l < T.nl; ++l) hs += T.dims[l];
   if (mode == ROWS_VALUES) {
-    if (T.ln) return M < 1280 && np > (f64 ? 150e3 : 200e3);
-    return M < 2560 && np > (M < 16 ? 100e3 : 150e3);
+    const int c = row_chain(T);
+    if (M < 16 && c > (!f64 && T.ln ? 35 : 17)) return true;
+    if (f64) return (c > 60 && (M < 2300 || (M > 4096 && M < 7000))) || (T.ln ? c > 33 && M < 1300 : c > 28 && M < 2300);
+    return T.ln ? c > 64 && M < 2560 : (c > 28 && M < 4608) || (c > 60 && M < 7000);
   }
   if (mode == ROWS_FIT) {
     if (T.ln) return M > (f64 ? 8192 : 16384) || (M > 2048 && hs * hs * hs * M > (f64 ? 5.6e11 : 1.2e12)) || (f64 && np > 200e3);

@@ -16,8 +16,9 @@ pytestmark = pytest.mark.gpu
 # FP32: values of order one from 512-term products at 6e-8 each; FP64 as the other critic tests
 @pytest.mark.parametrize("precision,tol", [("fp64", 1e-12), ("fp32", 1e-5)])
 @pytest.mark.parametrize("model,hidden,layer_norm,rows", [
-    ("mtu", [400, 200], False, (1, 33, 2559, 2560)), ("mtu", [512, 511], True, (1, 33, 1279, 1280)),
-    ("humanoid", [400, 200], False, (15, 16)), ("mtu", [512], False, (31, 2561))])
+    ("mtu", [400, 200], False, (1, 33, 2299, 2300, 4097, 6999, 7000)), ("ant", [512, 511], True, (1, 33, 2559, 2560)),
+    ("humanoid", [400, 200], False, (15, 16, 4607, 4608)), ("humanoid", [400, 200], True, (15, 1299, 1300)),
+    ("mtu", [512], False, (31, 2300)), ("ant", [256, 256], False, (15, 16))])
 def test_values(model, hidden, layer_norm, rows, precision, tol):
     name, od = MODEL[model]
     dims = [od] + hidden + [1]
