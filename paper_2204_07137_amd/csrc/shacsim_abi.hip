@@ -1081,6 +1081,7 @@ static int run_forward(SimHandle* h, const SimForwardIO* io, void* stream) {
   int rc = build_forward_args<T>(h, io, A);
   if (rc) return rc;
   int bad = do_prep(A, stream);
+  A.mus_few = A.N <= SIM_CUS;
   bad |= do_window(A, 0, h->opt.path == SIM_PATH_PLAIN, h->substeps, h->nv, h->m64.n_mtu > 0, h->opt.lanes_per_env,
                    stream);
   return bad ? launch_failed() : SIM_OK;
@@ -1091,6 +1092,7 @@ static int run_adjoint(SimHandle* h, const SimAdjointIO* io, void* stream) {
   WinArgsT<T> A;
   int rc = build_adjoint_args<T>(h, io, A);
   if (rc) return rc;
+  A.mus_few = A.N <= SIM_CUS;
   if (do_window(A, 1, h->opt.path == SIM_PATH_PLAIN, h->substeps, h->nv, h->m64.n_mtu > 0, h->opt.lanes_per_env,
                 stream))
     return launch_failed();

@@ -512,7 +512,11 @@ __device__ __forceinline__ void lds_add6(real* dst, sv w) {
 // lanes' additions per cycle: with four 152-muscle environments on a CU they took 16.9 k cycles of
 // the forward substep's 74 k and 63.9 k of its adjoint's 204 k; the schedule takes 13 k and 23 k.
 // Models beyond the schedule's capacity (more runs per unit or pass, or pairs, than it has room
-// for) keep the atomics.
+// for) keep the atomics, and so does the forward where a CU holds one environment (mus_few): the
+// atomics of one wavefront do not queue behind others' there, and a forward window of 256
+// environments takes 2.24 ms with them and 2.39 ms along the schedule (h = 2; 384 environments 2.51
+// and 2.47 ms, 1024 3.02 and 2.53 ms).  The adjoint's three tables are ahead along the schedule
+// already with one (2.84 against 2.65 ms on the tape path).
 template <class L>
 __device__ __forceinline__ real* mus_fm(L& E, int b) { return &E.mus[b * 6]; }
 template <class L>
@@ -548,7 +552,7 @@ __device__ __forceinline__ int run_slot(mus_u16x4 s, int run) {
 template <class L>
 __device__ __forceinline__ void muscle_wrenches(const Scal* __restrict__ m, L& E, int ln) {
   const MusSched* __restrict__ MS = m->mus;
-  const bool sched = MS != nullptr;
+  const bool sched = MS != nullptr && !((m->mus_nch >> 30) & 1);
   if (sched) {
     if (ln < 6) E.mus[ln * (SIM_MUS_SLOTS + 1) + SIM_MUS_SLOTS] = RL(0.0);
   } else {

@@ -940,7 +940,7 @@ __global__ __launch_bounds__(256) void k_log_std_grad(const real* __restrict__ d
 }
 
 // ---------------------------------------------------------------- launches
-#define MR_CUS 256
+#define MR_CUS SIM_CUS
 static MlpNet mlp_net(const ThetaArgsT<real>& T) {
   MlpNet N = {};
   N.M = T.M;

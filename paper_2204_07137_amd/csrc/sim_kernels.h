@@ -159,7 +159,7 @@ enum { KP_ANY = -1, KP_TAPE = 0, KP_FC = 1, KP_CKPT = 2 };
 // KP_CKPT (checkpoints, with or without the factor cache) or KP_ANY.
 template <int NV, class L, int PATH = KP_ANY>
 __device__ __forceinline__ void window_fwd_body(const WinArgs& A, int env, L& E) {
-  const Scal scl = load_scal(A.model);
+  const Scal scl = load_scal(A.model, L::kMtu > 0 ? A.mus_few : 0);
   const Scal* m = &scl;
   int ln = grp_lane<L::kLanes>();
   JointRegs jr;
@@ -354,7 +354,7 @@ template <int NV, class L, int PATH = KP_ANY>
 __device__ __forceinline__ void window_adj_body(const WinArgs& A, int env, L& E) {
   const bool use_tape = PATH == KP_TAPE || (PATH == KP_ANY && A.tape_full);
   const bool use_fc = L::kMtu == 0 && (PATH == KP_FC || (PATH == KP_ANY && A.fc));
-  const Scal scl = load_scal(A.model);
+  const Scal scl = load_scal(A.model, L::kMtu > 0 ? A.mus_few : 0);
   const Scal* m = &scl;
   int ln = grp_lane<L::kLanes>();
   JointRegs jr;

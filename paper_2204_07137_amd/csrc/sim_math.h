@@ -20,19 +20,20 @@ struct Scal {
   int tape_nw;           // 16-byte chunks of a packed tape entry
   int fc_nw;             // 16-byte chunks of a factor-cache entry
   unsigned int tree_chain, tree_multi;   // the subtree sums' frames (tree_sum)
-  int mus_nch;           // chunks of the muscles' schedule per pass, 4 bits each: forward, then adjoint
+  int mus_nch;           // chunks of the muscles' schedule per pass, 4 bits each: forward, then adjoint;
+                         // bit 30: the forward's wrenches by atomics (muscle_wrenches)
   real dt_sub, g, kn, kd, kt, mu, klim, chol_thr;
   real tau_act, fl_w, vmax, term_h;
   const DevModel* tab;   // the model's tables (muscle paths) in global memory
   const MusSched* mus;   // the muscles' summation schedule, or null
 };
-__device__ __forceinline__ Scal load_scal(const DevModel* __restrict__ m) {
+__device__ __forceinline__ Scal load_scal(const DevModel* __restrict__ m, int mus_few = 0) {
   Scal s;
   s.J = m->J; s.nq = m->nq; s.nv = m->nv; s.na = m->na; s.nc = m->nc; s.ns = m->ns; s.od = m->od;
   s.task = m->task; s.floating = m->floating; s.has_last_action = m->has_last_action;
   s.substeps = m->substeps; s.max_depth = m->max_depth;
   s.tree_chain = m->tree_chain; s.tree_multi = m->tree_multi;
-  s.mus_nch = m->mus_nch;
+  s.mus_nch = m->mus_nch | mus_few << 30;
   s.dt_sub = m->dt_sub; s.g = m->g; s.kn = m->kn; s.kd = m->kd; s.kt = m->kt; s.mu = m->mu; s.klim = m->klim;
   s.chol_thr = m->chol_thr;
   s.n_mtu = m->n_mtu; s.n_motor = m->n_motor; s.nck = m->nck;

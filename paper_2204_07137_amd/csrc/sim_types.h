@@ -13,6 +13,7 @@
 #define SIM_MAXAM 160    // actions of muscle-driven models (motors + muscle excitations)
 #define SIM_MAXMTU 160   // muscle-tendon units
 #define SIM_MAXMPT 6     // path points per muscle-tendon unit
+#define SIM_CUS 256      // compute units
 #define SIM_MAXOBS 288   // observation width
 #define SIM_MAXHID 512   // MLP width
 #define SIM_MAXL 4       // MLP linear layers
@@ -233,6 +234,7 @@ struct WinArgsT {
   // written by the forward, read by the adjoint's input VJP
   T* hid;
   int hid_w;
+  int mus_few;      // a CU holds at most one of the launch's environments (muscle_wrenches)
   // the window's loss: per env [N] and the sum over envs [1] (forward, optional)
   T* loss_env;
   T* loss;
@@ -298,7 +300,7 @@ struct ThetaArgsT {
 // Row chunks of k_mlp_wgrad (sim_gemm.h), which takes every layer's weight gradient in one launch of
 // a wave per 32 x 32 tile and chunk: enough waves for two on every SIMD, at least 64 rows each.
 #define SIM_WG_T 32
-#define SIM_WG_WAVES (2 * 4 * 256)
+#define SIM_WG_WAVES (2 * 4 * SIM_CUS)
 static inline int sim_wgrad_tiles(int n_out, int n_in) {
   return ((n_out + SIM_WG_T - 1) / SIM_WG_T) * ((n_in + SIM_WG_T - 1) / SIM_WG_T);
 }

@@ -74,6 +74,27 @@ def test_muscle_sums(n, runs):
     assert relnorm(ad["dL_ds0"], ref["dL_ds0"]) < 1e-9
 
 
+# the forward's sums by atomics (at most 256 environments, one per CU) and along the schedule (more)
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("n,runs", [(1, 2), (36, 4), (64, 2), (65, 2), (160, 2), (64, 3), (8, 5)])
+def test_muscle_sums_of_few_and_many_environments(n, runs, precision):
+    print(f"[sums] {n} units of {runs} runs, 256 and 257 environments, {precision}", flush=True)
+    md, h = _arms(n, runs), 2
+    rng = np.random.default_rng(6)
+    s0 = np.concatenate([rng.normal(0, 0.1, (257, 1)), rng.uniform(-0.5, 0.5, (257, 1)), rng.normal(0, 0.3, (257, 2)),
+                         rng.uniform(0.0, 1.0, (257, n))], 1)
+    u = rng.uniform(0.05, 0.95, (h, 257, n))
+    critic = [(rng.normal(size=(1, 4 + n)), np.zeros(1))]
+    ends = []
+    for N in (256, 257):
+        sim = P.Sim(md, N, h, None, [4 + n, 1], ckpt_interval=2, precision=precision)
+        ends.append(_np(sim.forward(s0[:N], None, critic, actions_in=np.ascontiguousarray(u[:, :N])))["s_h"])
+        sim.close()
+    ref = oracle_window_grads(md, s0[:2], h, None, critic, actions=u[:, :2], n_total=2)["s_h"]
+    assert np.isfinite(ends[0]).all() and np.array_equal(ends[0], ends[1][:256])
+    assert relnorm(ends[0][:2], ref) < (1e-11 if precision == "fp64" else 1e-5)
+
+
 def _tree(n, free_root, N, h):
     md = wl.models.chain(n=n, free_root=free_root, substeps=4)
     rng = np.random.default_rng(n)
