@@ -470,8 +470,8 @@ int sim_obs_stats_update_ws(const void* obs, long rows, int dim, double count, v
 
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight
  * serving loops, harnesses that forbid allocation): sim_critic_values without a workspace.
- * The critic's hidden-layer activations live in a static device array of 64 MiB that the
- * library holds on every GPU it runs on until the process ends, so rows x (sum of the critic's
+ * The critic's hidden-layer activations, where a network's size has them leave the chip, live in a
+ * static device array of 64 MiB that the library holds on every GPU it runs on until the process ends, so rows x (sum of the critic's
  * hidden widths) x element size must fit in 64 MiB (after 256-byte alignment of each layer's
  * block; the humanoid's 76-128-128-1 critic in FP32: 65536 rows), else SIM_E_WORKSPACE before
  * any launch.  Arguments, layouts and results as for sim_critic_values; nothing is allocated

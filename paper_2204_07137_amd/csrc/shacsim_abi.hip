@@ -30,8 +30,9 @@ static int fail(int code, const std::string& msg) {
 }
 
 // ---------------------------------------------------------------- allocation-free critic values
-// The scratch of sim_critic_values_noalloc (the critic's hidden-layer activations) is a
-// static device array, held by every GPU the library runs on until the process ends.  In host
+// The scratch of sim_critic_values_noalloc (the critic's hidden-layer activations, which networks
+// that go layer by layer write to memory) is a static device array, held by every GPU the library
+// runs on until the process ends.  In host
 // code its name is only a host-side stand-in: the device address is taken once per device at
 // set-up (sim_create, or the entry point's first call on a device) with hipGetSymbolAddress,
 // and only that address is passed to kernels.

@@ -367,7 +367,8 @@ struct RowsArgs {
 // issues 208 of them per wave forward) and, with few rows, the chain of memory latencies
 // (arguments, rows, each layer's first weights).  Keeping a tile's rows in LDS through all layers
 // replaces one launch and one round trip of the activations per layer: 33792 rows of that
-// critic's values take 33 us (54 TFLOP/s of the 150 a large FP32 product reaches), 92 us before.
+// critic's values take 33 us (54 TFLOP/s of the 150 a large FP32 product reaches), 92 us before (in
+// cache; 85 and 142 us on rows and weights that are not).
 // waves per SIMD the register allocation aims at
 constexpr int rows_waves(int rt, int mode, bool ln) {
   if (sizeof(real) == 8) return mode == ROWS_VALUES ? 2 : 1;
@@ -993,7 +994,8 @@ static int launch_rows_as(const RowsArgs& g, int blocks, size_t lds, hipStream_t
 }
 
 // 32 rows a block where that still gives every CU a block, else 16 (also where 32 rows of the
-// widest layer take more than 64 KB of LDS); with layer normalisation the blocks are as many as
+// widest layer take more than 64 KB of LDS: with up to 144 KB a CU has one block, and values of
+// 32768 rows took 1.1 times as long for 512 columns and 1.5 for 400); with layer normalisation the blocks are as many as
 // the partial-sum buffer holds.  *n_blocks: the blocks launched (rows of lnpart), *n_tiles: the row
 // tiles (entries of loss_part).
 template <int MODE>

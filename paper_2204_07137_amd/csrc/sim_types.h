@@ -177,8 +177,8 @@ struct MlpArgsT {
   const T* lnb[SIM_MAXL];      // [out] bias of hidden layer l (caller)
 };
 
-// the gain / bias partial sums of a layer-normalised network's rows pass are sized for this many
-// blocks of the widest layer
+// blocks of the layer-normalisation adjoint layer by layer; the gain / bias partial sums of the row
+// tiles are sized for as many of the widest layer
 #define SIM_LN_BLOCKS 256
 
 // phases of the window kernels' profile (a build with -DSIM_PHASE_PROFILE; ids in sim_math.h)
