@@ -10,7 +10,7 @@ from oracle import learn as OL
 
 pytestmark = pytest.mark.gpu
 
-MODEL = {"ant": ("ant", 37), "humanoid": ("humanoid", 76), "mtu": ("mtu_humanoid", 280)}
+MODEL = {"cartpole": ("cartpole", 5), "ant": ("ant", 37), "humanoid": ("humanoid", 76), "mtu": ("mtu_humanoid", 280)}
 # losses; changes of the parameters and moments: those of the other fits
 TOL = {"fp32": (1e-4, 2e-2), "fp64": (1e-9, 1e-8)}
 
@@ -62,10 +62,11 @@ def test_layer_normalised_fit_of_uneven_minibatches(rows):
 
 
 # fused tiles of 32 rows two to a CU (280 inputs: 58 KB), and one to a CU (256-128: 63 to 126 KB); of
-# 16 rows one to a CU (57 and 62 KB)
+# 16 rows one to a CU (57 and 62 KB); 464-128 takes all but 128 bytes of a CU's LDS
 @pytest.mark.parametrize("model,hidden,layer_norm,precision,rows,n_mb", [
     ("mtu", [64, 64], False, "fp32", 8193, 1), ("humanoid", [256, 128], False, "fp32", 8192, 1),
     ("humanoid", [256, 128], True, "fp32", 8207, 1), ("humanoid", [256, 128], False, "fp64", 8193, 1),
-    ("mtu", [64, 64], False, "fp64", 100, 3), ("ant", [128, 64], True, "fp64", 100, 3)])
+    ("mtu", [64, 64], False, "fp64", 100, 3), ("ant", [128, 64], True, "fp64", 100, 3),
+    ("cartpole", [464, 128], True, "fp32", 8200, 1)])
 def test_fused_forms(model, hidden, layer_norm, precision, rows, n_mb):
     check_fit(model, hidden, layer_norm, precision, rows, n_mb, 2)
