@@ -26,7 +26,7 @@ def check_fit(model, hidden, layer_norm, precision, rows, n_mb, n_iter):
     name, od = MODEL[model]
     dims = [od] + hidden + [1]
     dt = torch.float32 if precision == "fp32" else torch.float64
-    sim = P.Sim(wl.model_by_name(name), 4, 1, None, dims, ckpt_interval=16, precision=precision, layer_norm=layer_norm)
+    sim = P.Sim(wl.model_by_name(name), 4, 1, None, dims, ckpt_interval=1, precision=precision, layer_norm=layer_norm)
     rng = np.random.default_rng(rows)
     f32 = lambda x: np.asarray(x).astype(np.float32).astype(np.float64)
     net = [tuple(f32(x) for x in pair) for pair in wl.mlp_params(dims, 3)]
